@@ -151,8 +151,8 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
 
 // ---------------------------------------------------------------- write path
 
-// Up to two (pool, input) pairs written by one launch, pair blockIdx.z: the
-// K and V pools of one append share the page lists and the launch.
+// Up to two (pool, input) pairs written by one launch: the K and V pools of
+// one append share the page lists and the launch.
 struct ScatterArgs {
   void* pool[2];
   const void* in[2];
@@ -166,133 +166,360 @@ struct ScatterArgs {
   int64_t num_pool_pages;
   int32_t num_seqs;
   int32_t num_kv_heads;
-  int32_t head_dim;
+  int32_t n_pairs;
+  int32_t seq_blocks;    // workgroups by sequence and pool (partly touched pages)
+  int32_t tile_blocks;   // workgroups per pool for the whole pages' tiles
+};
+// Sequences whose tiles one workgroup sums.
+constexpr int kTileSeqs = 4096;
+
+// A whole tile (16 tokens of one head): read from the dense input with 16-byte
+// loads, transposed in the wave's own LDS buffer and written in stored order,
+// 16 bytes per lane.
+template <typename W, int D>
+struct TileWriter {
+  static constexpr int E = 16 / (int)sizeof(W);   // elements per 16-byte vector
+  static constexpr int VPT = D / E;               // vectors per token and head
+  static constexpr int NV = 16 * VPT / 64;        // vectors per lane for a tile
+  static constexpr int KROW = 17;                 // K staging: vector (j, t) at j * KROW + t
+  // V staging: the tile in stored order, [D][16] elements, row c held at row
+  // c ^ ((c / E) & RMASK): the rows written by one instruction (dims
+  // j*E + q of four dim groups j) then fall in different 32-byte bank groups.
+  static constexpr int RMASK = 128 / (16 * (int)sizeof(W)) - 1;
+  static constexpr int BUF = VPT * KROW > D * 16 / E ? VPT * KROW : D * 16 / E;   // 16-byte vectors
+
+  static __device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+
+  // This lane's vectors of a tile: K in input order (dims fastest); V with the
+  // token fastest across lanes, so that one instruction's 16 lanes of a dim
+  // group fill the 16 slots of one staged row.
+  template <bool V>
+  static __device__ __forceinline__ void load(const W* src, int64_t row, u32x4_t (&v)[NV], int lane) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int idx = lane + 64 * i;
+      const int tok = V ? idx % 16 : idx / VPT, j = V ? idx / 16 : idx % VPT;
+      v[i] = *reinterpret_cast<const u32x4_t*>(src + tok * row + j * E);
+    }
+  }
+
+  template <bool V>
+  static __device__ __forceinline__ void store(const u32x4_t (&v)[NV], W* dst, u32x4_t* kst, int lane) {
+    if constexpr (!V) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int idx = lane + 64 * i, tok = idx / VPT, j = idx % VPT;
+        kst[j * KROW + tok] = v[i];
+      }
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {    // K: [D/E][16][E], vector idx = (j, t)
+        const int idx = lane + 64 * i;
+        *reinterpret_cast<u32x4_t*>(dst + idx * E) = kst[(idx / 16) * KROW + idx % 16];
+      }
+    } else {
+      W* vst = reinterpret_cast<W*>(kst);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int idx = lane + 64 * i, tok = idx % 16, j = idx / 16;
+        const int slot = v_token_at_slot(tok);   // the permutation is its own inverse
+        const W* e = reinterpret_cast<const W*>(&v[i]);
+#pragma unroll
+        for (int q = 0; q < E; ++q) vst[((j * E + q) ^ (j & RMASK)) * 16 + slot] = e[q];
+      }
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {    // V: [D][16], vector idx = (dim c, slot group)
+        const int idx = lane + 64 * i, c = idx / (16 / E), part = idx % (16 / E);
+        *reinterpret_cast<u32x4_t*>(dst + idx * E) =
+            *reinterpret_cast<const u32x4_t*>(vst + (c ^ ((c / E) & RMASK)) * 16 + part * E);
+      }
+    }
+    wave_sync();
+  }
+};
+
+// n < 16 (or unaligned) tokens of one page, every head, written straight from
+// the input by the whole workgroup: 16-byte vectors for K, whose vector (dim
+// group, token) holds one token; single elements of 8-byte loads for V, whose
+// slots interleave tokens. Other slots are never written. src: the first of
+// the tokens (dense rows of H * D elements); t: its slot in the page.
+template <typename W, int D, bool V>
+__device__ __forceinline__ void write_part_page(const W* __restrict__ src, W* __restrict__ page, int n, int t, int H) {
+  constexpr int E = 16 / (int)sizeof(W);
+  constexpr int VPT = D / E;
+  constexpr int kUnroll = 4;   // loads in flight per thread before their stores
+  const int threads = 256;
+  if constexpr (!V) {
+    const int per_tok = H * VPT, total = n * per_tok;
+    for (int i0 = threadIdx.x; i0 < total; i0 += kUnroll * threads) {
+      u32x4_t v[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int idx = i0 + u * threads;
+        if (idx < total) v[u] = *reinterpret_cast<const u32x4_t*>(src + (int64_t)idx * E);
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int idx = i0 + u * threads;
+        if (idx >= total) break;
+        const int tok = idx / per_tok, hv = idx % per_tok;   // hv = head * VPT + dim group
+        *reinterpret_cast<u32x4_t*>(page + ((int64_t)hv * 16 + t + tok) * E) = v[u];
+      }
+    }
+  } else {
+    typedef W wvec_t __attribute__((ext_vector_type(8 / (int)sizeof(W))));
+    constexpr int EV = 8 / (int)sizeof(W);
+    const int total = n * (H * D / EV);   // token fastest: neighbouring lanes write one dim row
+    for (int i0 = threadIdx.x; i0 < total; i0 += kUnroll * threads) {
+      wvec_t v[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int idx = i0 + u * threads;
+        if (idx < total) {
+          const int tok = idx % n, hc = idx / n;
+          v[u] = *reinterpret_cast<const wvec_t*>(src + (int64_t)tok * H * D + hc * EV);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int idx = i0 + u * threads;
+        if (idx >= total) break;
+        const int tok = idx % n, hc = idx / n;
+        W* dst = page + (int64_t)hc * EV * 16 + v_token_at_slot(t + tok);
+#pragma unroll
+        for (int q = 0; q < EV; ++q) dst[q * 16] = v[u][q];
+      }
+    }
+  }
+}
+
+// Pages touched by tokens start .. start + count - 1 of one sequence: a first
+// and a last one that may be partial, and nfull whole pages from slot f0.
+struct PageRange {
+  int first, last, f0, nfull;
+  bool head, tail;   // the first / last page is partly touched (last != first)
+  __device__ __forceinline__ PageRange(int start, int count) {
+    const int end = start + count;
+    first = start / 16;
+    last = (end - 1) / 16;
+    head = (start & 15) != 0 || end < 16 * (first + 1);
+    tail = last > first && (end & 15) != 0;
+    f0 = first + (head ? 1 : 0);
+    nfull = last - (tail ? 1 : 0) - f0 + 1;
+  }
 };
 
 // The inverse of the gather: tokens start .. start + count - 1 of each
 // sequence are written from the dense input into their (page, head) tiles.
-// Blocks (x, y) take sequence x (grid-stride) and its touched tiles; each of
-// the block's four waves owns one tile at a time (tiles y*4 + wave, stepping
-// by gridDim.y*4), so only the pages the range touches are visited and a
-// decode append costs one tile per head whatever the sequence's length.
-// A full tile (16 touched tokens) is read with 16-byte loads, transposed in
-// the wave's own LDS buffer and written back as the tile's 4 KB (bf16,
-// d 128) in stored order, 16 bytes per lane. A partly touched tile (a
-// decode append, the ends of a chunk) is written straight from the input:
-// 16-byte vectors for K, whose vector (dim group, token) holds one token;
-// single elements for V, whose slots interleave tokens. Untouched slots are
-// never written. Words of the element's width keep every bit pattern.
-template <typename W, int D>
-__global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
-  constexpr int E = 16 / (int)sizeof(W);   // elements per 16-byte vector
-  constexpr int VPT = D / E;               // vectors per token and head
-  constexpr int TV = 16 * VPT;             // vectors per tile
-  constexpr int NV = TV / 64;              // vectors per lane for a full tile
-  constexpr int KROW = 17;                 // K staging: vector (j, t) at j * KROW + t
-  constexpr int KBUF = VPT * KROW;         // 16-byte vectors
-  // V staging: the tile in stored order, [D][16] elements, row c held at row
-  // c ^ ((c / E) & RMASK): the rows written by one instruction (dims
-  // j*E + q of four dim groups j) then fall in different 32-byte bank groups.
-  constexpr int RMASK = 128 / (16 * (int)sizeof(W)) - 1;
-  constexpr int VBUF = D * 16 / E;
-  constexpr int BUF = KBUF > VBUF ? KBUF : VBUF;
-  __shared__ u32x4_t stage[4][BUF];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+//
+// What bounds it: a decode append is a chain of dependent loads (the
+// sequence's range and page list, then the page id beside the token) and one
+// store; a chunk is an HBM copy. The host knows neither, the ranges being on
+// the device, so the grid has two kinds of workgroups:
+//  * one for each sequence and pool, launched first: its partly touched first
+//    and last pages, all heads at once. An append costs one short chain, and
+//    no workgroup of this kind looks at another sequence.
+//  * tile_blocks per pool for the whole pages: each sums the whole-page tiles
+//    of all sequences and its waves take equal contiguous runs of them, so one
+//    long range among many short ones spreads over the chip. Without a whole
+//    page it ends after the sum.
+// Kernel times against a grid of equal workgroups per sequence (bf16, d 128, 8
+// heads, K and V): 240 appends and 16 chunks of 64-512 tokens 66 -> 18 us, 992
+// appends and 32 chunks 298 -> 54 us, 32 ragged chunks 27 -> 20 us, 64 appends
+// 5.7 -> 4.3 us, 32 chunks of 512 tokens 31 us (4.3 TB/s) with both.
+template <typename W, int D, bool V>
+__device__ __forceinline__ void scatter_seq(const ScatterArgs& a, int z, int first_seq, int stride) {
   const int H = a.num_kv_heads;
   const int64_t row = (int64_t)H * D;      // input elements per token
-  W* pool = static_cast<W*>(a.pool[blockIdx.z]);
-  const W* in = static_cast<const W*>(a.in[blockIdx.z]);
-  const bool v_layout = a.v_layout[blockIdx.z] != 0;
-  u32x4_t* kst = stage[wave];
-  W* vst = reinterpret_cast<W*>(stage[wave]);
-  for (int seq = blockIdx.x; seq < a.num_seqs; seq += gridDim.x) {
+  const W* in = static_cast<const W*>(a.in[z]);
+  W* pool = static_cast<W*>(a.pool[z]);
+  for (int seq = first_seq; seq < a.num_seqs; seq += stride) {
     const int start = a.seq_start[seq], count = a.seq_count[seq];
+    const int base = a.seq_page_indptr[seq], next = a.seq_page_indptr[seq + 1];
+    const int64_t off = a.in_token_offset[seq];
     if (count <= 0) continue;
-    const int base = a.seq_page_indptr[seq];
-    const int npages = a.seq_page_indptr[seq + 1] - base;
-    if (start < 0 || (int64_t)start + count > (int64_t)npages * 16) {
-      if (blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && a.error_flag) a.error_flag[0] = 1;
+    if (start < 0 || (int64_t)start + count > (int64_t)(next - base) * 16) {
+      if (z == 0 && threadIdx.x == 0 && a.error_flag) a.error_flag[0] = 1;
       continue;
     }
-    const int first = start / 16, last = (start + count - 1) / 16;
-    const int ntiles = (last - first + 1) * H;
-    for (int k = blockIdx.y * 4 + wave; k < ntiles; k += gridDim.y * 4) {
-      const int pslot = first + k / H, h = k % H;
+    const PageRange r(start, count);
+#pragma nounroll
+    for (int side = 0; side < 2; ++side) {
+      if (!(side ? r.tail : r.head)) continue;
+      const int pslot = side ? r.last : r.first;
       const int pid = a.page_ids[base + pslot];
+      if (pid < 0 || pid >= a.num_pool_pages) {
+        if (threadIdx.x == 0 && a.error_flag) a.error_flag[0] = 1;
+        continue;
+      }
+      const int lo = max(start, pslot * 16), hi = min(start + count, pslot * 16 + 16);
+      write_part_page<W, D, V>(in + (off + (lo - start)) * row, pool + (int64_t)pid * H * 16 * D, hi - lo,
+                               lo - pslot * 16, H);
+    }
+  }
+}
+
+// Inclusive sum over the lanes of a wave: shifts by 1, 2, 4 and 8 inside each
+// row of 16 lanes, then the last lane of a row to the next row (rows 1 and 3)
+// and lane 31 to the upper half.
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
+
+// The range of one sequence, and its whole-page tiles (none where the range
+// does not fit its page list: its own workgroup flags that).
+struct SeqRange {
+  int start, base, tiles, f0;
+  int64_t off;
+  __device__ __forceinline__ SeqRange(const ScatterArgs& a, int seq) {
+    start = a.seq_start[seq];
+    const int count = a.seq_count[seq];
+    base = a.seq_page_indptr[seq];
+    const int next = a.seq_page_indptr[seq + 1];
+    off = a.in_token_offset[seq];
+    const PageRange r(start, count);
+    f0 = r.f0;
+    const bool fits = count > 0 && start >= 0 && (int64_t)start + count <= (int64_t)(next - base) * 16;
+    tiles = fits ? r.nfull * a.num_kv_heads : 0;
+  }
+};
+
+// Whole pages: the tiles of up to kTileSeqs sequences, cut into equal
+// contiguous runs, one per wave. Up to 64 sequences every wave sums by itself,
+// one sequence per lane, and finds its run in the lanes' registers, without a
+// barrier or a second look at the metadata (32 chunks of 512 tokens, K and V:
+// 30.6 us; by the workgroup 33.5). More are summed by the workgroup, thread i
+// those of sequences i, i + 256, ..., in LDS (1024 appends: 18 us, against
+// 22.7 when every wave sums all of them). A sequence with fewer than 16 new
+// tokens has no whole page: only its count is read.
+template <typename W, int D, bool V>
+__device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int z, int s0, int n_seqs, int turn, int turns,
+                                              u32x4_t* stage, int (&sums)[260], int wave, int lane) {
+  const int H = a.num_kv_heads;
+  const int64_t row = (int64_t)H * D;
+  const bool by_wave = n_seqs <= 64;
+  int mine = 0, l_start = 0, l_base = 0, l_f0 = 0, upto, total;
+  int64_t l_off = 0;
+  if (by_wave) {
+    if (lane < n_seqs) {
+      const SeqRange r(a, s0 + lane);
+      mine = r.tiles;
+      l_start = r.start;
+      l_base = r.base;
+      l_f0 = r.f0;
+      l_off = r.off;
+    }
+    if (!__any(mine > 0)) return;
+    upto = wave_inclusive_sum(mine);
+    total = __builtin_amdgcn_readlane(upto, 63);
+  } else {
+    constexpr int kAhead = 4;   // counts in flight per thread
+    for (int i0 = threadIdx.x; i0 < n_seqs; i0 += kAhead * 256) {
+      int count[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) count[u] = i0 + 256 * u < n_seqs ? a.seq_count[s0 + i0 + 256 * u] : 0;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (count[u] >= 16) mine += SeqRange(a, s0 + i0 + 256 * u).tiles;
+    }
+    if (!__syncthreads_or(mine)) return;
+    upto = wave_inclusive_sum(mine);
+    if (lane == 63) sums[256 + wave] = upto;
+    __syncthreads();
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      upto += w < wave ? sums[256 + w] : 0;
+      total += sums[256 + w];
+    }
+    sums[threadIdx.x] = upto;
+    __syncthreads();
+  }
+  const int per = (int)(((int64_t)total + turns - 1) / turns);
+  int k = (int)min((int64_t)total, (int64_t)turn * per);
+  const int k_end = (int)min((int64_t)total, (int64_t)k + per);
+  while (k < k_end) {
+    int t, n, base, f0;
+    int64_t at;   // dense row of the sequence's token 0
+    if (by_wave) {
+      const int lo = __popcll(__ballot(upto <= k));   // the lane whose sequence holds tile k
+      t = k - (lo ? __builtin_amdgcn_readlane(upto, lo - 1) : 0);
+      n = __builtin_amdgcn_readlane(mine, lo);
+      base = __builtin_amdgcn_readlane(l_base, lo);
+      f0 = __builtin_amdgcn_readlane(l_f0, lo);
+      at = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(l_off >> 32), lo) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)l_off, lo)) -
+           __builtin_amdgcn_readlane(l_start, lo);
+    } else {
+      int lo = 0;   // the thread whose sequences hold tile k
+#pragma unroll
+      for (int j = 0; j < 4; ++j) lo += __popcll(__ballot(sums[64 * j + lane] <= k));
+      t = k - (lo ? sums[lo - 1] : 0);
+      t = __builtin_amdgcn_readfirstlane(t);
+      int seq = s0 + lo;
+      SeqRange r(a, seq);
+      while (t >= r.tiles) {
+        t -= r.tiles;
+        seq += 256;
+        r = SeqRange(a, seq);
+      }
+      n = r.tiles;
+      base = r.base;
+      f0 = r.f0;
+      at = r.off - r.start;
+    }
+    // tiles t .. t_end - 1 of one sequence, heads innermost
+    const int t_end = min(n, t + (k_end - k));
+    k += t_end - t;
+    const W* in = static_cast<const W*>(a.in[z]) + at * row;
+#pragma nounroll
+    for (; t < t_end; ++t) {
+      const int pslot = f0 + t / H, h = t % H;
+      const int pid = a.page_ids[base + pslot];
+      u32x4_t v[TileWriter<W, D>::NV];
+      TileWriter<W, D>::template load<V>(in + (int64_t)pslot * 16 * row + (int64_t)h * D, row, v, lane);
       if (pid < 0 || pid >= a.num_pool_pages) {
         if (lane == 0 && a.error_flag) a.error_flag[0] = 1;
         continue;
       }
-      const int t0 = pslot * 16;
-      const int lo_t = max(start, t0), hi_t = min(start + count, t0 + 16);   // touched tokens
-      const int n = hi_t - lo_t;
-      const W* src = in + (a.in_token_offset[seq] + (lo_t - start)) * row + (int64_t)h * D;
-      W* dst = pool + ((int64_t)pid * H + h) * 16 * D;
-      if (n == 16 && !v_layout) {
-        u32x4_t v[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int idx = lane + 64 * i, tok = idx / VPT, j = idx % VPT;
-          v[i] = *reinterpret_cast<const u32x4_t*>(src + tok * row + j * E);
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int idx = lane + 64 * i, tok = idx / VPT, j = idx % VPT;
-          kst[j * KROW + tok] = v[i];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {    // K: [D/E][16][E], vector idx = (j, t)
-          const int idx = lane + 64 * i;
-          *reinterpret_cast<u32x4_t*>(dst + idx * E) = kst[(idx / 16) * KROW + idx % 16];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      } else if (n == 16) {
-        // Token fastest across lanes: one instruction's 16 lanes of a dim
-        // group fill the 16 slots of one staged row.
-        u32x4_t v[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int idx = lane + 64 * i, tok = idx % 16, j = idx / 16;
-          v[i] = *reinterpret_cast<const u32x4_t*>(src + tok * row + j * E);
-        }
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int idx = lane + 64 * i, tok = idx % 16, j = idx / 16;
-          const int slot = v_token_at_slot(tok);   // the permutation is its own inverse
-          const W* e = reinterpret_cast<const W*>(&v[i]);
-#pragma unroll
-          for (int q = 0; q < E; ++q) vst[((j * E + q) ^ (j & RMASK)) * 16 + slot] = e[q];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {    // V: [D][16], vector idx = (dim c, slot group)
-          const int idx = lane + 64 * i, c = idx / (16 / E), part = idx % (16 / E);
-          *reinterpret_cast<u32x4_t*>(dst + idx * E) =
-              *reinterpret_cast<const u32x4_t*>(vst + (c ^ ((c / E) & RMASK)) * 16 + part * E);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      } else if (!v_layout) {
-        for (int idx = lane; idx < n * VPT; idx += 64) {
-          const int tok = idx / VPT, j = idx % VPT, t = lo_t - t0 + tok;
-          *reinterpret_cast<u32x4_t*>(dst + (j * 16 + t) * E) =
-              *reinterpret_cast<const u32x4_t*>(src + tok * row + j * E);
-        }
-      } else {
-        for (int idx = lane; idx < n * D; idx += 64) {
-          const int tok = idx / D, c = idx % D, t = lo_t - t0 + tok;
-          dst[c * 16 + v_token_at_slot(t)] = src[tok * row + c];
-        }
-      }
+      TileWriter<W, D>::template store<V>(v, static_cast<W*>(a.pool[z]) + ((int64_t)pid * H + h) * 16 * D, stage, lane);
     }
+  }
+}
+
+template <typename W, int D>
+__global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
+  __shared__ u32x4_t stage[4][TileWriter<W, D>::BUF];
+  __shared__ int sums[260];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if ((int)blockIdx.x < a.seq_blocks) {
+    const int z = (int)blockIdx.x % a.n_pairs, seq = (int)blockIdx.x / a.n_pairs, stride = a.seq_blocks / a.n_pairs;
+    if (a.v_layout[z]) scatter_seq<W, D, true>(a, z, seq, stride);
+    else scatter_seq<W, D, false>(a, z, seq, stride);
+    return;
+  }
+  const int z = ((int)blockIdx.x - a.seq_blocks) % a.n_pairs;
+  const int tb = ((int)blockIdx.x - a.seq_blocks) / a.n_pairs;   // of a.tile_blocks for this pool
+  const int groups = (a.num_seqs + kTileSeqs - 1) / kTileSeqs;
+  for (int g = tb % groups; g < groups; g += a.tile_blocks) {
+    // the workgroups of this group, and this one's turn among them
+    const int of = a.tile_blocks >= groups ? (a.tile_blocks - g + groups - 1) / groups : 1;
+    const int s0 = g * kTileSeqs, n = min(a.num_seqs - s0, kTileSeqs);
+    const int turn = tb / groups * 4 + wave;
+    if (a.v_layout[z]) scatter_tiles<W, D, true>(a, z, s0, n, turn, of * 4, stage[wave], sums, wave, lane);
+    else scatter_tiles<W, D, false>(a, z, s0, n, turn, of * 4, stage[wave], sums, wave, lane);
+    __syncthreads();   // the sums are overwritten for the next group
   }
 }
 
@@ -389,13 +616,17 @@ halo_status_t launch_scatter(const halo_attn_params_t* params, ScatterArgs g, in
       return fail(HALO_ERR_INVALID_ARGUMENT, "pools and inputs must be 16-byte aligned");
   g.num_pool_pages = params->num_pool_pages;
   g.num_kv_heads = params->num_kv_heads;
-  g.head_dim = params->head_dim;
+  g.n_pairs = n_pairs;
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  // One x-block per sequence (grid-stride past 65536), enough y-blocks per
-  // sequence that a call fills the chip with about 2048 workgroups.
-  const int bx = std::min(g.num_seqs, 65536);
-  const dim3 grid(bx, std::min(std::max(2048 / (bx * n_pairs), 1), 2048), n_pairs);
+  // A workgroup per sequence and pool (grid-stride past 65536 sequences), and
+  // 512 of four waves for the whole pages: with 1024 a batch of appends waits
+  // for them (64 sequences: 4.3 -> 4.7 us), with 256 a chunk's copies have
+  // too few loads in flight (32 chunks of 512 tokens: 30.8 -> 39 us).
+  constexpr int kTileBlocks = 512;
+  g.seq_blocks = std::min(g.num_seqs, 65536) * n_pairs;
+  g.tile_blocks = kTileBlocks / n_pairs;
+  const dim3 grid(g.seq_blocks + kTileBlocks);
   const bool d128 = params->head_dim == 128;
   if (params->kv_dtype == HALO_BF16) {
     if (d128) hipLaunchKernelGGL((scatter_kernel<uint16_t, 128>), grid, dim3(256), 0, st, g);

@@ -88,6 +88,28 @@ def test_scatter_bit_exact(gpu_lib, dtype, D, kind):
     assert np.array_equal(got, exp)
 
 
+@pytest.mark.parametrize("n_seqs,dtype,D", [(1, torch.bfloat16, 128), (64, torch.float32, 64), (65, torch.bfloat16, 64),
+                                            (300, torch.float32, 128), (4100, torch.bfloat16, 64)])
+@pytest.mark.parametrize("kind", [halo.HALO_POOL_K, halo.HALO_POOL_V])
+def test_scatter_long_ranges_among_appends(gpu_lib, n_seqs, dtype, D, kind):
+    """A few ragged chunks among single-token appends, at the batch sizes
+    where the whole pages are summed by a wave (up to 64), by a workgroup
+    (several sequences per thread past 256) and in two groups (past 4096);
+    three heads, so the waves' runs of tiles end inside a page."""
+    print(f"case: scatter {n_seqs} sequences {dtype} d{D} kind {kind}", flush=True)
+    rng = np.random.default_rng(n_seqs + kind)
+    chunks = {0: (5, 100), n_seqs // 2: (16, 48), n_seqs - 1: (3, 77)}   # sequence: (start, count)
+    perm = rng.permutation(n_seqs + 30).astype(np.int32)
+    seqs, at = [], 0
+    for i in range(n_seqs):
+        start, count = chunks.get(i, (int(rng.integers(0, PAGE)), 1))
+        n = (start + count + PAGE - 1) // PAGE
+        seqs.append((perm[at:at + n], start, count))
+        at += n
+    got, exp, _ = _scatter(dtype, D, 3, len(perm), seqs, kind, rng)
+    assert np.array_equal(got, exp)
+
+
 @pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.float32, 64)])
 def test_scatter_kv_equals_two_single_pool_calls(gpu_lib, dtype, D):
     """The two-pool call writes exactly what the two single-pool calls write,
