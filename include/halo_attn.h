@@ -396,7 +396,7 @@ typedef struct {
   int64_t num_query_rows;     /* rows of q / o */
   int64_t distinct_kv_tokens; /* sum of segment lengths, each segment once */
   int64_t visible_pairs;      /* sum over query rows and q heads of visible keys */
-  int32_t num_wide_items;     /* wide work items (one 8-wave workgroup, <= 256 rows) */
+  int32_t num_wide_items;     /* wide work items (one 8-wave workgroup, <= 256 rows; prefill: 4 waves, <= 128) */
   int32_t wide_row_blocks;    /* 1 when the plan has wide items (32 query rows per wave), else 0 */
 } halo_plan_stats_t;
 

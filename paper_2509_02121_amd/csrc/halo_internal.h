@@ -17,6 +17,17 @@ constexpr int kRowsPerItem = 16;
 // A wide item is one workgroup of kWideWaves waves of 32 query rows each.
 constexpr int kWideWaves = 8;
 constexpr int kMaxWideRows = kWideWaves * 32;
+// Wide items of up to kSmallWideRows rows, alone in a launch (prefill), run in
+// workgroups of kSmallWideWaves waves, two of which share a CU: one's start,
+// masked steps and epilogue overlap the other's products, and a chunk's rows
+// are cut more finely. Against one 8-wave workgroup per CU (bf16, 32/8 heads,
+// d 128): 8 requests of 128 tokens on 1024 cached ones 43 -> 30 us, one of 901
+// on 4999 176 -> 125 us, 32 of 512 alone 178 -> 157 us, on 4096 shared ones
+// 1205 -> 1163 us; at d 64 the last 809 -> 763 us. Decode launches mix wide and
+// narrow items and stay with kWideWaves (70B-shaped batch 916 us, with 4-wave
+// workgroups 944).
+constexpr int kSmallWideWaves = 4;
+constexpr int kSmallWideRows = kSmallWideWaves * 32;
 // Narrow items per workgroup (one per wave): 8 for bf16, 4 for fp32.
 inline int narrow_items_per_block(halo_dtype_t dt) { return dt == HALO_BF16 ? 8 : 4; }
 // Compute units of an MI355X: a decode plan with no wide items launches one
@@ -164,6 +175,7 @@ struct halo_plan {
   int32_t n_wide = 0;
   int32_t wide_rb = 0;       // 1 when the plan has wide items (32 rows per wave), else 0
   int32_t wide_group = 1;    // wide items that share pages, kept on one XCD
+  bool small_wide = false;   // every item is wide and of at most kSmallWideRows rows
   int32_t n_narrow_blocks = 0;  // workgroups the narrow items are dealt to (a multiple of 8)
   int32_t narrow_slots = 0;     // item slots per narrow workgroup (slot k: wave k)
   int32_t n_shared_items = 0;

@@ -14,9 +14,9 @@
 //     contiguous bytes), so every MFMA operand is a direct 1 KB-per-wave load
 //     from one or two pages. The QK output layout is already the PV B
 //     operand (no lane exchange).
-//   * wide: up to 256 query rows (8 waves x 32) sharing one key stream,
-//     staged once per workgroup through an LDS ring by direct global-to-LDS
-//     loads, on v_mfma_f32_32x32x16_bf16.
+//   * wide: up to 256 query rows (8 waves x 32; 128 in a prefill, see
+//     wide_kernel) sharing one key stream, staged once per workgroup through
+//     an LDS ring by direct global-to-LDS loads, on v_mfma_f32_32x32x16_bf16.
 // merge_kernel: exact log-sum-exp combination of partial results over
 //   disjoint key ranges (the merge that makes shared == unshared), in its own
 //   launch so the kernel boundary makes every partial visible (an in-kernel
@@ -575,21 +575,22 @@ __device__ __forceinline__ void narrow_block(const AttnArgs& a, int block) {
 }
 
 // ---------------------------------------------------------------- wide items
-// A wide item holds up to kWideWaves * 32 query rows of one kv head against
-// a span list: a workgroup of kWideWaves waves, 32 rows per wave, all rows
-// sharing the key stream. Used for the grouped prefix pass
-// (many rows share one segment, §2 intra-batch prefix sharing) and for
-// chunked prefill (§4.1).
+// A wide item holds up to W * 32 query rows of one kv head against a span
+// list: a workgroup of W waves (kWideWaves, or kSmallWideWaves in
+// wide_kernel), 32 rows per wave, all rows sharing the key stream. Used for
+// the grouped prefix pass (many rows share one segment, §2 intra-batch prefix
+// sharing) and for chunked prefill (§4.1).
 //
-// Loads. Each 32-key step's K and V (two pages) are read once per
-// workgroup, by direct global-to-LDS loads into a ring of kWideStages step
-// images, so no registers hold data in transit. A step image is
-// 2 * D/32 + D/16 blocks of 1 KB (16 KB at d = 128); block k is written by
-// one load instruction whose lane L fetches the 16 bytes that lane L of
-// every wave later reads with one ds_read_b128 at L * 16, so every LDS read
-// is sequential and conflict-free. With c = L % 32, h = L / 32:
-//   K block s (dims 16s..16s+15):   page c / 16, key c % 16, unit 2s + h
-//   V block (page g, dims 32b..+31): page g, dim 32b + c, slots 8h..8h+7
+// Loads. Each 32-key step's K and V (two pages) are read once per workgroup,
+// by direct global-to-LDS loads into a ring of S step images, so no registers
+// hold data in transit. A step image is 2 * D/32 + D/16 blocks of 1 KB (16 KB
+// at d = 128), each from one page. With c = L % 32, h = L / 32 of lane L:
+//   K block (page g, units 4j..4j+3): as stored; lane L fetches key L % 16 of
+//     unit 4j + L / 16. The fragment of dims 16s..16s+15 is then, per lane,
+//     page c / 16, key c % 16, unit 2s + h: four runs of 256 bytes;
+//   V block (page g, dims 32b..+31): lane L fetches dim 32b + c, slots
+//     8h..8h+7, and every lane reads its own 16 bytes back.
+// Both reads are free of bank conflicts.
 //
 // Products use v_mfma_f32_32x32x16_bf16, the shape that reaches the bf16
 // peak on gfx950 (measured 2.48 PFLOP/s, against 1.39 for 16x16x32):
@@ -609,13 +610,13 @@ __device__ __forceinline__ void narrow_block(const AttnArgs& a, int block) {
 // 2^kRescaleLog2); the result is the same softmax, and the accumulator
 // rescale runs only on the rare steps where some row moves.
 constexpr float kRescaleLog2 = 8.f;
-constexpr int kWideStages = 6;
 
-// Bytes of the wide items' LDS ring: kWideStages step images of
-// 2 * D/32 + D/16 blocks of 1 KB.
-template <int D> constexpr int wide_ring_bytes() { return kWideStages * (D / 16 + 2 * (D / 32)) * 1024; }
+// Bytes of the wide items' LDS ring: S step images of 2 * D/32 + D/16 blocks
+// of 1 KB.
+template <int D, int S> constexpr int wide_ring_bytes() { return S * (D / 16 + 2 * (D / 32)) * 1024; }
 
-template <int D, typename TO>
+// A workgroup of W waves and an S-stage ring.
+template <int D, typename TO, int W, int S>
 __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_t* smem) {
   using T = __bf16;
   using F = bf16x8_t;
@@ -623,15 +624,15 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
   constexpr int NO = D / 32;                      // 32-dim output blocks
   constexpr int kBlocks = NK + 2 * NO;            // 1 KB blocks per step image
   constexpr int kStepBytes = kBlocks * 1024;
-  static_assert(kBlocks % kWideWaves == 0, "step blocks must split evenly over the waves");
-  constexpr int kLoadsPerWave = kBlocks / kWideWaves;
-  constexpr int S = kWideStages;
-  static_assert(S >= 5 && S % 2 == 0, "the ring needs >= 5 stages, an even count keeps tile parity static");
+  static_assert(kBlocks % W == 0, "step blocks must split evenly over the waves");
+  constexpr int kLoadsPerWave = kBlocks / W;
+  static_assert(S >= 4 && S % 2 == 0, "the ring needs >= 4 stages, an even count keeps tile parity static");
   constexpr int64_t kTile = 16 * D;
-  static_assert(S * kStepBytes == wide_ring_bytes<D>(), "ring size");
+  static_assert(S * kStepBytes == (wide_ring_bytes<D, S>()), "ring size");
   uint8_t (*lds)[kStepBytes] = reinterpret_cast<uint8_t (*)[kStepBytes]>(smem);
 
   const int wave = threadIdx.x >> 6;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);   // on the scalar unit, for addresses
   const int lane = threadIdx.x & 63;
   const int c = lane & 31;
   const int h = lane >> 5;
@@ -689,45 +690,48 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
     p.has1 = t_next + 16 < cur.ke;
     p.full = t_next + kKeysPerStep <= cur.ke && !cur.causal;
     p.pid0 = __builtin_amdgcn_readlane(cur.vpid, j);
-    p.pid1 = p.has1 ? __builtin_amdgcn_readlane(cur.vpid, j + 1) : p.pid0;
+    p.pid1 = __builtin_amdgcn_readlane(cur.vpid, j + (p.has1 ? 1 : 0));
     t_next += kKeysPerStep;
     return p;
   };
 
-  // ---- loads: this wave writes blocks wave + kWideWaves * k of a step image.
-  // Per lane: K or V, which page of the step, and the element offset inside
-  // that page's tile. Page bases are computed on the scalar unit.
-  int ld_off[kLoadsPerWave];
-  bool ld_v[kLoadsPerWave], ld_p1[kLoadsPerWave];
-#pragma unroll
-  for (int k = 0; k < kLoadsPerWave; ++k) {
-    const int blk = wave + kWideWaves * k;
-    ld_v[k] = blk >= NK;
-    if (!ld_v[k]) {
-      ld_p1[k] = c >= 16;
-      ld_off[k] = ((2 * blk + h) * 16 + (c & 15)) * 8;
-    } else {
-      const int g = (blk - NK) / NO, b = (blk - NK) % NO;
-      ld_p1[k] = g == 1;
-      ld_off[k] = (32 * b + c) * 16 + 8 * h;
-    }
-  }
-  // Byte offsets of the step's two pages, forced onto the scalar unit (the
-  // per-lane choice between them is then one select per half).
+  // ---- loads: this wave writes blocks wave + W * k of a step image. A block
+  // lies in one page, so its address is a wave-uniform base and a lane offset
+  // that never changes: the addresses cost no vector instructions (with lanes
+  // of one block in both pages, ~20 a step and wave beside ~100 of softmax:
+  // chunked prefill 1200 -> 1163 us, short chunks 88 -> 79 us).
+  const uint32_t k_off = lane * 16, v_off = c * 32 + h * 16;
+  // (readfirstlane keeps a base whole: the compiler would otherwise add the
+  // lane offset to the pool's address first and the page's to that, per lane)
   auto uniform64 = [](int64_t x) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
   };
   auto issue = [&](const StepPos& p, uint8_t* img) {
-    const int64_t o0 = uniform64((int64_t)p.pid0 * page_stride);
-    const int64_t o1 = uniform64((int64_t)p.pid1 * page_stride);
+    const int64_t o0 = uniform64((int64_t)(uint32_t)p.pid0 * page_stride * (int64_t)sizeof(T));
+    const int64_t o1 = uniform64((int64_t)(uint32_t)p.pid1 * page_stride * (int64_t)sizeof(T));
 #pragma unroll
     for (int k = 0; k < kLoadsPerWave; ++k) {
-      const T* base = (ld_v[k] ? vbase : kbase) + ld_off[k];
-      __builtin_amdgcn_global_load_lds(base + (ld_p1[k] ? o1 : o0), img + (wave + kWideWaves * k) * 1024, 16, 0, 0);
+      // kind and page of block uwave + W * k: known here when W divides the
+      // blocks of a page
+      constexpr bool kStatic = (NK / 2) % W == 0;
+      const int blk = (kStatic ? 0 : uwave) + W * k;
+      const bool is_k = blk < NK;
+      const int of_kind = is_k ? blk : blk - NK;
+      const bool p1 = of_kind >= NK / 2;
+      const int in_page = of_kind % (NK / 2) + (kStatic ? uwave : 0);
+      uint32_t off = is_k ? k_off : v_off;
+      asm volatile("" : "+v"(off));   // (not widened outside the loop: the load adds it itself)
+      const uint8_t* base = reinterpret_cast<const uint8_t*>(is_k ? kbase : vbase) + in_page * 1024;
+      __builtin_amdgcn_global_load_lds(
+          reinterpret_cast<const uint8_t*>(uniform64(reinterpret_cast<int64_t>(base) + (p1 ? o1 : o0))) + off,
+          img + (uwave + W * k) * 1024, 16, 0, 0);
     }
   };
+  // K fragment s of a step image: this lane's key and units 2s + h.
+  const int k_rd = (c >> 4) * (NK / 2) * 1024 + h * 256 + (c & 15) * 16;
+  auto k_at = [&](const uint8_t* img, int s) { return img + k_rd + s / 2 * 1024 + s % 2 * 512; };
 
   float m = kNegInf, lsum = 0.f;
   f32x16_t acc[NO];
@@ -739,10 +743,9 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
 
   // Q K^T of one step (one accumulation chain over the 16-dim slices).
   auto qk = [&](const uint8_t* img, f32x16_t& sacc) {
-    const uint8_t* rd = img + lane * 16;
     F kf[NK];
 #pragma unroll
-    for (int s = 0; s < NK; ++s) kf[s] = __builtin_bit_cast(F, *reinterpret_cast<const u32x4_t*>(rd + s * 1024));
+    for (int s = 0; s < NK; ++s) kf[s] = __builtin_bit_cast(F, *reinterpret_cast<const u32x4_t*>(k_at(img, s)));
     f32x16_t sn = f32x16_t{};
 #pragma unroll
     for (int s = 0; s < NK; ++s) sn = mma32(kf[s], qf[s], sn);
@@ -839,10 +842,9 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
   // (alpha) and applied afterwards.
   auto fast_iter = [&](F (&vf)[2][NO], const uint8_t* img_qk, const uint8_t* img_v, const F (&pf_prev)[2],
                        const f32x16_t& sacc_cur, f32x16_t& sacc_nxt, F (&pf_cur)[2], float& alpha) {
-    const uint8_t* rk = img_qk + lane * 16;
     F kf[NK];
 #pragma unroll
-    for (int s = 0; s < NK; ++s) kf[s] = __builtin_bit_cast(F, *reinterpret_cast<const u32x4_t*>(rk + s * 1024));
+    for (int s = 0; s < NK; ++s) kf[s] = __builtin_bit_cast(F, *reinterpret_cast<const u32x4_t*>(k_at(img_qk, s)));
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -1015,13 +1017,15 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
 // blocks (dealt longest first, so its tail is short ones). Within a role
 // the block index modulo 8 still names the XCD (xcd_remap, and the
 // planner's dealing of narrow items to XCDs, rely on it).
+constexpr int kMixedStages = 6;
+
 template <typename T, int D, typename TO, int RB>
 __global__ __launch_bounds__(64 * block_waves<T>())
 __attribute__((amdgpu_waves_per_eu(block_waves<T>() / 4)))
 void attn_kernel(AttnArgs a) {
   static_assert(RB == 0 || block_waves<T>() == kWideWaves, "wide items need kWideWaves-wave blocks");
   // the wide role's LDS ring (narrow items use no LDS)
-  constexpr int kSmem = RB > 0 ? wide_ring_bytes<D>() : 16;
+  constexpr int kSmem = RB > 0 ? wide_ring_bytes<D, kMixedStages>() : 16;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kSmem];
   const int b = blockIdx.x;
   const int x = b & 7, r = b >> 3;
@@ -1034,7 +1038,7 @@ void attn_kernel(AttnArgs a) {
     const int w_upto = cyc < sp ? (int)((int64_t)(cyc + 1) * ws / sp) : ws;
     if (w_upto > w_before) {
       const int item = xcd_remap((w_before * kSeCycle + q) * 8 + x, a.wide_group);
-      if (item < a.n_wide) wide_item<D, TO>(a, item, smem);
+      if (item < a.n_wide) wide_item<D, TO, kWideWaves, kMixedStages>(a, item, smem);
       return;
     }
     narrow_block<T, D, TO>(a, ((cyc - w_upto) * kSeCycle + q) * 8 + x);
@@ -1042,6 +1046,18 @@ void attn_kernel(AttnArgs a) {
     (void)smem;
     narrow_block<T, D, TO>(a, b);
   }
+}
+
+// Wide items of at most kSmallWideRows rows and nothing else (prefill): two
+// workgroups of four waves share a CU.
+constexpr int kSmallStages = 4;
+
+template <int D, typename TO>
+__global__ __launch_bounds__(64 * kSmallWideWaves) __attribute__((amdgpu_waves_per_eu(2)))
+void wide_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[wide_ring_bytes<D, kSmallStages>()];
+  const int item = xcd_remap(blockIdx.x, a.wide_group);
+  if (item < a.n_wide) wide_item<D, TO, kSmallWideWaves, kSmallStages>(a, item, smem);
 }
 
 // ---------------------------------------------------------------- merge
@@ -1221,7 +1237,7 @@ int lcm_int(int a, int b) {
 }
 
 template <typename T, int D, typename TO>
-void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, hipStream_t stream) {
+void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, bool small_wide, hipStream_t stream) {
   const int rb = sizeof(T) == 2 ? wide_rb : 0;
   // whole dispatch cycles of wide rounds, each a multiple of wide_group rounds
   args.wide_blocks =
@@ -1234,7 +1250,10 @@ void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, hipStr
   const int grid = args.wide_blocks + args.narrow_blocks;
   if (grid > 0) {
     if constexpr (sizeof(T) == 2) {
-      if (rb > 0)
+      if (rb > 0 && small_wide)
+        hipLaunchKernelGGL((wide_kernel<D, TO>), dim3(pad_to(args.n_wide, 8 * args.wide_group)),
+                           dim3(64 * kSmallWideWaves), 0, stream, args);
+      else if (rb > 0)
         hipLaunchKernelGGL((attn_kernel<T, D, TO, 1>), dim3(grid), dim3(64 * W), 0, stream, args);
       else
         hipLaunchKernelGGL((attn_kernel<T, D, TO, 0>), dim3(grid), dim3(64 * W), 0, stream, args);
@@ -1304,15 +1323,15 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
   const bool out_f32 = p.out_dtype == HALO_F32;
   if (p.kv_dtype == HALO_BF16) {
     if (D == 128) {
-      if (out_f32) launch_attention<__bf16, 128, float>(args, margs, plan->wide_rb, st);
-      else launch_attention<__bf16, 128, __bf16>(args, margs, plan->wide_rb, st);
+      if (out_f32) launch_attention<__bf16, 128, float>(args, margs, plan->wide_rb, plan->small_wide, st);
+      else launch_attention<__bf16, 128, __bf16>(args, margs, plan->wide_rb, plan->small_wide, st);
     } else {
-      if (out_f32) launch_attention<__bf16, 64, float>(args, margs, plan->wide_rb, st);
-      else launch_attention<__bf16, 64, __bf16>(args, margs, plan->wide_rb, st);
+      if (out_f32) launch_attention<__bf16, 64, float>(args, margs, plan->wide_rb, plan->small_wide, st);
+      else launch_attention<__bf16, 64, __bf16>(args, margs, plan->wide_rb, plan->small_wide, st);
     }
   } else {
-    if (D == 128) launch_attention<float, 128, float>(args, margs, plan->wide_rb, st);
-    else launch_attention<float, 64, float>(args, margs, plan->wide_rb, st);
+    if (D == 128) launch_attention<float, 128, float>(args, margs, plan->wide_rb, plan->small_wide, st);
+    else launch_attention<float, 64, float>(args, margs, plan->wide_rb, plan->small_wide, st);
   }
   return hip_check("attention launch");
 }

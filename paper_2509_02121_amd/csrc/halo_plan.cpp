@@ -15,7 +15,7 @@
 // log-sum-exp merge, rows with exactly one write their final result directly.
 //
 // Prefill (§4.1, prefix caching): each item holds the (query, head) rows of
-// one request and one kv head -- up to 256 in a wide item for bf16, 16 in a
+// one request and one kv head -- up to 128 in a wide item for bf16, 16 in a
 // narrow item otherwise -- and walks all of that request's keys, the cached
 // prefix first and its own chunk last, causally; results are final.
 
@@ -418,11 +418,12 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         }
     }
   } else {
-    // Prefill: bf16 rows go to wide items of up to kMaxWideRows (query, head) rows.
+    // Prefill: bf16 rows go to wide items of kSmallWideRows (query, head) rows.
     const bool wide = p.kv_dtype == HALO_BF16 && opt.wide != 0;
     plan->wide_rb = wide ? 1 : 0;
     plan->wide_group = 1;
-    const int rows_per = wide ? (opt.wide_rows > 0 ? opt.wide_rows : kMaxWideRows) : kRowsPerItem;
+    const int rows_per = wide ? (opt.wide_rows > 0 ? opt.wide_rows : kSmallWideRows) : kRowsPerItem;
+    plan->small_wide = wide && rows_per <= kSmallWideRows;
     for (int r = 0; r < R; ++r) {
       const int32_t n = f.q_len[r];
       if (n == 0) continue;
