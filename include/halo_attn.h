@@ -230,7 +230,10 @@ halo_status_t halo_prefix_attn_decode(const halo_plan_t* plan, const void* devic
 /* Chunked prefill over cached prefixes (§4.1 prefix-caching discount):
  * every chunk query attends to its path's earlier segments and causally to
  * its own chunk. Arguments as for decode; the plan must be a prefill plan.
- * workspace may be NULL when the plan's workspace_bytes is 0. */
+ * A plan of few items cuts their keys into pieces and needs a workspace for
+ * their results (O and LSE in fp32). Without one (NULL, not 256-byte aligned
+ * or smaller than the plan's workspace_bytes) the call runs the items uncut:
+ * the same results up to summation order, later. */
 halo_status_t halo_prefix_attn_prefill(const halo_plan_t* plan, const void* device_meta,
                                        const void* q, const void* k_pool, const void* v_pool,
                                        void* o, float* lse,

@@ -64,6 +64,18 @@ struct Item {
   int32_t pad[5];
 };
 constexpr int32_t kItemStream = 1;
+// A piece of a prefill item's keys: row k's partial result, fp32 whatever the
+// output type, goes to slot part_base + k.
+constexpr int32_t kItemPiece = 2;
+
+// A prefill item whose keys were cut into pieces: its rows, and the part_base
+// of each piece (merge_bases[part_begin .. part_begin + n_parts)).
+struct MergeItem {
+  int32_t row_begin;
+  int32_t n_rows;
+  int32_t part_begin;
+  int32_t n_parts;
+};
 
 // What the 64 lanes of a narrow item's wavefront read at its start, one
 // 32-bit word each (256 bytes): the q_row of each of its (up to 16) rows, a
@@ -125,6 +137,13 @@ struct MetaLayout {
   size_t merge_rows = 0;     // int32 [n_merge] output row (q_row) per merge entry
   size_t merge_indptr = 0;   // int32 [n_merge + 1]
   size_t merge_parts = 0;    // int32 [n_parts] partial slot ids (merge_indptr[m] + k)
+  // A prefill plan whose items are cut into pieces: the merge of the pieces,
+  // and the items uncut (for a call without the workspace of the pieces).
+  size_t merge_items = 0;    // MergeItem [n_merge_items]
+  size_t merge_bases = 0;    // int32 [n_pieces]
+  size_t whole_items = 0;    // as items, item_recs and wide_items
+  size_t whole_recs = 0;
+  size_t whole_wide = 0;
   size_t total = 0;
 };
 
@@ -187,6 +206,11 @@ struct halo_plan {
   int64_t n_part_rows = 0;
   int64_t n_part_slots = 0;     // workspace slots (>= n_part_rows)
   int32_t merge_k0 = 0;         // partials per merge entry at slots k * n_merge + m
+  int32_t n_merge_items = 0;    // prefill items cut into pieces (0: none)
+  int32_t merge_item_rows = 0;  // most rows of one of them
+  int64_t merged_rows = 0;      // their rows
+  int32_t n_whole_wide = 0;     // the uncut items, as n_wide and n_narrow_blocks
+  int32_t n_whole_blocks = 0;
   int64_t distinct_kv_tokens = 0;
   int64_t visible_pairs = 0;
   size_t workspace_bytes = 0;

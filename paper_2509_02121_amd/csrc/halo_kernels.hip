@@ -534,7 +534,13 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, const Item& it, cons
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
   const float lse2 = lsum > 0.f ? m + __log2f(lsum) : kNegInf;
   if (it.part_base >= 0) {
-    if (has_row) {
+    if (sizeof(T) == 4 && has_row && (it.flags & kItemPiece)) {   // (bf16 pieces are wide items)
+      const int64_t prow = (int64_t)it.part_base + col;
+      float* dst = static_cast<float*>(a.part_o) + prow * D + 4 * grp;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) store4(dst + 16 * b, acc[b] * inv);
+      if (grp == 0) a.part_lse[prow] = lse2;
+    } else if (has_row) {
       const int64_t prow = row.slot;
       TO* dst = static_cast<TO*>(a.part_o) + prow * D + 4 * grp;
 #pragma unroll
@@ -985,7 +991,16 @@ __device__ __forceinline__ void wide_item(const AttnArgs& a, int item_id, uint8_
   if (computes && r < it.n_rows) {
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const float lse2 = l > 0.f ? m + __log2f(l) : kNegInf;
-    if (it.part_base >= 0) {
+    if (W == kSmallWideWaves && (it.flags & kItemPiece)) {
+      const int64_t prow = (int64_t)it.part_base + r;
+      float* dst = static_cast<float*>(a.part_o) + prow * D + 4 * h;
+#pragma unroll
+      for (int b = 0; b < NO; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          store4(dst + 32 * b + 8 * q, f32x4_t{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]} * inv);
+      if (h == 0) a.part_lse[prow] = lse2;
+    } else if (it.part_base >= 0) {
       const int64_t prow = row.slot;
       TO* dst = static_cast<TO*>(a.part_o) + prow * D + 4 * h;
 #pragma unroll
@@ -1208,6 +1223,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void m
   if (t == 0 && a.lse) a.lse[q_row] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : kNegInf;
 }
 
+// The rows of prefill items whose keys were cut into pieces, by the same rule.
+// A piece's partials are contiguous (row k of the item at its part_base + k,
+// fp32), so a row's are found from the item's list of bases: one group of D / 4
+// threads per row, 16 bytes of each partial per thread, up to 8 partials in
+// flight. Bound by the bytes of the partials.
+struct MergeItemArgs {
+  const float* part_o;
+  const float* part_lse;
+  const MergeItem* items;
+  const int32_t* bases;
+  const Row* rows;
+  void* o;
+  float* lse;
+  int32_t blocks_per_item;
+};
+
+template <int D, typename TO>
+__global__ __launch_bounds__(256) void merge_items_kernel(MergeItemArgs a) {
+  constexpr int TPR = D / 4;
+  constexpr int RPB = 256 / TPR;
+  constexpr int kBatch = 8;
+  const MergeItem mi = a.items[blockIdx.x / a.blocks_per_item];
+  const int r = (int)(blockIdx.x % a.blocks_per_item) * RPB + (int)threadIdx.x / TPR;
+  const int t = threadIdx.x % TPR;
+  if (r >= mi.n_rows) return;
+  const int q_row = a.rows[mi.row_begin + r].q_row;
+  float mx = kNegInf, wsum = 0.f;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < mi.n_parts; k0 += kBatch) {
+    float l[kBatch];
+    f32x4_t v[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      l[k] = kNegInf;
+      v[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (k0 + k < mi.n_parts) {
+        const int64_t slot = (int64_t)a.bases[mi.part_begin + k0 + k] + r;
+        l[k] = a.part_lse[slot];
+        v[k] = *reinterpret_cast<const f32x4_t*>(a.part_o + slot * D + 4 * t);
+      }
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) m_new = fmaxf(m_new, l[k]);
+    if (m_new == kNegInf) continue;   // a row that sees no key of these pieces
+    const float alpha = mx == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mx - m_new);
+    acc *= alpha;
+    wsum *= alpha;
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const float w = __builtin_amdgcn_exp2f(l[k] - m_new);
+      wsum += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(w, v[k][e], acc[e]);
+    }
+    mx = m_new;
+  }
+  const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+  store4(static_cast<TO*>(a.o) + (int64_t)q_row * D + 4 * t, acc * inv);
+  if (t == 0 && a.lse) a.lse[q_row] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : kNegInf;
+}
+
 // ---------------------------------------------------------------- host side
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -1268,6 +1345,13 @@ void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, bool s
   }
 }
 
+template <int D, typename TO>
+void launch_merge_items(MergeItemArgs args, int n_items, int most_rows, hipStream_t stream) {
+  constexpr int rpb = 256 / (D / 4);
+  args.blocks_per_item = (most_rows + rpb - 1) / rpb;
+  hipLaunchKernelGGL((merge_items_kernel<D, TO>), dim3(n_items * args.blocks_per_item), dim3(256), 0, stream, args);
+}
+
 halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const void* device_meta,
                             const void* q, const void* k_pool, const void* v_pool, void* o, float* lse,
                             void* workspace, size_t workspace_bytes, void* stream) {
@@ -1281,10 +1365,14 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
   if (!aligned16(q) || !aligned16(k_pool) || !aligned16(v_pool) || !aligned16(o) ||
       (reinterpret_cast<uintptr_t>(device_meta) & 255) != 0)
     return fail(HALO_ERR_INVALID_ARGUMENT, "q, k_pool, v_pool, o must be 16-byte aligned, device_meta 256-byte");
-  if (workspace_bytes < plan->workspace_bytes)
+  // a prefill without the workspace of its pieces runs its items uncut
+  const bool whole = plan->prefill && plan->n_merge_items > 0 &&
+                     (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
+                      workspace_bytes < plan->workspace_bytes);
+  if (!plan->prefill && workspace_bytes < plan->workspace_bytes)
     return fail(HALO_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(plan->workspace_bytes) +
                                                   " bytes, got " + std::to_string(workspace_bytes));
-  if (plan->workspace_bytes > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0))
+  if (!plan->prefill && plan->workspace_bytes > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0))
     return fail(HALO_ERR_INVALID_ARGUMENT, "workspace must be a 256-byte aligned device pointer");
 
   const halo_attn_params_t& p = plan->params;
@@ -1293,8 +1381,8 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
   const int D = p.head_dim;
   // partial O rows in the output element type, then their LSEs
   void* part_o = workspace;
-  const size_t part_elem = p.out_dtype == HALO_F32 ? 4 : 2;
-  float* part_lse = plan->n_part_slots
+  const size_t part_elem = plan->prefill || p.out_dtype == HALO_F32 ? 4 : 2;
+  float* part_lse = plan->n_part_slots && !whole
                         ? reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) +
                                                    align256((size_t)plan->n_part_slots * D * part_elem))
                         : nullptr;
@@ -1302,12 +1390,13 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
                 reinterpret_cast<const int32_t*>(m + L.seg_page_off),
                 reinterpret_cast<const int32_t*>(m + L.seg_len),
                 reinterpret_cast<const int32_t*>(m + L.page_ids),
-                reinterpret_cast<const Item*>(m + L.items),
-                reinterpret_cast<const ItemRec*>(m + L.item_recs),
-                reinterpret_cast<const Item*>(m + L.wide_items),
+                reinterpret_cast<const Item*>(m + (whole ? L.whole_items : L.items)),
+                reinterpret_cast<const ItemRec*>(m + (whole ? L.whole_recs : L.item_recs)),
+                reinterpret_cast<const Item*>(m + (whole ? L.whole_wide : L.wide_items)),
                 reinterpret_cast<const Span*>(m + L.spans),
                 reinterpret_cast<const Row*>(m + L.rows),
-                plan->n_items, plan->n_wide, 0, plan->n_narrow_blocks, plan->narrow_slots,
+                plan->n_items, whole ? plan->n_whole_wide : plan->n_wide, 0,
+                whole ? plan->n_whole_blocks : plan->n_narrow_blocks, plan->narrow_slots,
                 plan->wide_group, 0,
                 p.num_kv_heads, p.sm_scale * kLog2e};
   MergeArgs margs{part_o, part_lse,
@@ -1332,6 +1421,20 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
   } else {
     if (D == 128) launch_attention<float, 128, float>(args, margs, plan->wide_rb, plan->small_wide, st);
     else launch_attention<float, 64, float>(args, margs, plan->wide_rb, plan->small_wide, st);
+  }
+  if (plan->n_merge_items > 0 && !whole) {
+    const MergeItemArgs ma{static_cast<const float*>(part_o), part_lse,
+                           reinterpret_cast<const MergeItem*>(m + L.merge_items),
+                           reinterpret_cast<const int32_t*>(m + L.merge_bases),
+                           reinterpret_cast<const Row*>(m + L.rows), o, lse, 0};
+    const int n = plan->n_merge_items, rows = plan->merge_item_rows;
+    if (D == 128) {
+      if (out_f32) launch_merge_items<128, float>(ma, n, rows, st);
+      else launch_merge_items<128, __bf16>(ma, n, rows, st);
+    } else {
+      if (out_f32) launch_merge_items<64, float>(ma, n, rows, st);
+      else launch_merge_items<64, __bf16>(ma, n, rows, st);
+    }
   }
   return hip_check("attention launch");
 }

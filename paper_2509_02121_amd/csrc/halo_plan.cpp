@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <limits>
 #include <mutex>
 #include <new>
@@ -159,6 +160,112 @@ void pieces(int32_t seg, int32_t len, int32_t chunk, std::vector<Span>& out) {
     out.push_back(Span{seg, kb, std::min(len, kb + chunk), 0, 0, {0, 0, 0}});
 }
 
+// How a prefill plan cuts its items' keys: into equal pieces of at most
+// `length` 32-key steps, or (equal = false) into pieces of `length` steps and
+// a shorter last one. length 0: not at all.
+struct PieceCut {
+  int32_t length = 0;
+  bool equal = true;
+
+  // The end of each piece of an item of n steps.
+  void ends(int32_t n, std::vector<int32_t>& out) const {
+    out.clear();
+    if (length <= 0 || n <= length) {
+      out.push_back(n);
+      return;
+    }
+    const int32_t k = (n + length - 1) / length;
+    for (int32_t i = 1; i < k; ++i) out.push_back(equal ? (int32_t)((int64_t)n * i / k) : i * length);
+    // a last piece much shorter than the others costs more than it brings
+    if (!equal && n - out.back() < std::max(2, length / 8)) out.pop_back();
+    out.push_back(n);
+  }
+};
+
+// A prefill item as choose_pieces sees it.
+struct ItemSize {
+  int32_t steps;   // of 32 keys
+  int32_t rows;
+};
+
+// The cut of a prefill's items (those of one kv head) that an estimate of the
+// call's time likes best. The items are launched longest first, so the
+// estimate deals them greedily to the CUs.
+//
+// Wide items (us, bf16 d 128, measured): a CU works off 2 per item and 0.1 +
+// 0.1 per 32 rows and step, whether one workgroup or two share it; a lone
+// item's chain takes 5 + 0.65 per step (d 64: 0.66 and 0.75 of that per step).
+// fp32 items, four to a workgroup and one per SIMD: 3.5 + 2.4 per step (d 64:
+// 1.25). The merge launch takes 4, and the partial results, fp32, written and
+// read, move at 8 TB/s. Measured, uncut and cut: one request of 901 tokens on
+// 4999 cached ones 121 -> 102, of 64 on 5000 105 -> 23, of 8 on 5000 89 -> 15;
+// fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181 -> 132.
+PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int head_dim, bool wide) {
+  constexpr int32_t kMinItem = 16, kMinPiece = 4;        // steps: below, a piece is mostly its start and end
+  constexpr int64_t kMaxBytes = (int64_t)256 << 20;      // of partial results
+  const int64_t per_cu = wide ? 2 : 4;                   // items a CU holds at once
+  int64_t total = 0;
+  int32_t longest = 0;
+  for (const ItemSize& x : items) {
+    total += x.steps;
+    longest = std::max(longest, x.steps);
+  }
+  total *= n_kv_heads;
+  // (with many rounds of items the longest is a small part of the call)
+  if (longest < kMinItem || (int64_t)items.size() * n_kv_heads > 4 * per_cu * kNumCUs) return {};
+  const bool d128 = head_dim == 128;
+  const double row_step = wide ? (d128 ? 0.1 : 0.066) : (d128 ? 2.4 : 1.25);
+  const double chain_step = wide ? (d128 ? 0.65 : 0.49) : row_step;
+  std::vector<int32_t> ends;
+  std::vector<std::pair<double, int32_t>> parts;   // (CU time, steps)
+  std::vector<double> cus;
+  auto estimate = [&](const PieceCut& cut) {
+    parts.clear();
+    int64_t part_rows = 0;
+    double last = 0;
+    for (const ItemSize& x : items) {
+      cut.ends(x.steps, ends);
+      for (size_t k = 0; k < ends.size(); ++k) {
+        const int32_t n = ends[k] - (k ? ends[k - 1] : 0);
+        parts.emplace_back(wide ? 2.0 + n * row_step * (1 + (x.rows + 31) / 32) : 3.5 + n * row_step, n);
+        last = std::max(last, (wide ? 5.0 : 3.5) + n * chain_step);
+      }
+      if (ends.size() > 1) part_rows += (int64_t)ends.size() * x.rows;
+    }
+    part_rows *= n_kv_heads;
+    const int64_t bytes = part_rows * (head_dim + 1) * 4;
+    if (bytes > kMaxBytes) return std::numeric_limits<double>::infinity();
+    std::sort(parts.begin(), parts.end(), std::greater<std::pair<double, int32_t>>());
+    // a workgroup's items end together: wide ones are alone in theirs
+    const size_t group = wide ? 1 : 4;
+    cus.assign(std::max(1, kNumCUs / n_kv_heads), 0.0);   // min-heap of the CUs' end times
+    for (size_t i = 0; i < parts.size(); i += group) {
+      std::pop_heap(cus.begin(), cus.end(), std::greater<double>());
+      cus.back() += parts[i].first;
+      last = std::max(last, cus.back());
+      std::push_heap(cus.begin(), cus.end(), std::greater<double>());
+    }
+    return last + (part_rows ? 4.0 + 2.0 * bytes / 8e6 : 0.0);
+  };
+  PieceCut best;
+  double least = 0.95 * estimate(best);   // a cut has to bring something
+  for (int rounds = 1; rounds <= 4; ++rounds)
+    for (int64_t at_once : {kNumCUs * per_cu / 2, kNumCUs * per_cu}) {
+      PieceCut cut;
+      cut.length = (int32_t)std::max<int64_t>(kMinPiece, (total + at_once * rounds - 1) / (at_once * rounds));
+      if (cut.length >= longest) continue;
+      for (bool equal : {true, false}) {
+        cut.equal = equal;
+        const double t = estimate(cut);
+        if (t < least) {
+          least = t;
+          best = cut;
+        }
+      }
+    }
+  return best;
+}
+
 // The planner's large arrays are thread-local and keep their capacity from
 // one call to the next (returned empty): a decode loop plans every step, and
 // first touches of fresh multi-megabyte allocations (page faults) cost about
@@ -277,8 +384,15 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     bool shared;
     bool wide;
     int32_t chunk = -1;   // shared items: id of the (piece, kv head) whose pages they read
+    // prefill: rows in prefill_rows (in place of `rows`), and for a piece its
+    // place among the pieces' part_bases
+    int32_t row_begin = 0, n_rows = 0, part_at = -1;
   };
   auto& protos = scratch<std::vector<Proto>, 0>();
+  auto& prefill_rows = scratch<std::vector<Row>, 1>();
+  std::vector<Proto> whole;   // prefill: the items before they were cut into pieces (empty: not cut)
+  std::vector<MergeItem> merge_items;     // prefill: the items cut into pieces, and each piece's part_base
+  std::vector<int32_t> merge_bases;
   int32_t n_chunks = 0;
 
   if (!prefill) {
@@ -437,26 +551,25 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         prefix_keys += f.seg_len[s];
       }
       plan->visible_pairs += ((int64_t)n * prefix_keys + (int64_t)n * (n + 1) / 2) * Hq;
-      for (int g = 0; g < Hkv; ++g) {
-        std::vector<Row> rows;
-        for (int32_t i = 0; i < n; ++i)
-          for (int j = 0; j < G; ++j)
-            rows.push_back(Row{(int32_t)((tok0[r] + i) * Hq + g * G + j), i, -1, -1});
-        for (size_t rb = 0; rb < rows.size(); rb += rows_per) {
+      // row blocks outermost, kv heads innermost: the launch order (longest
+      // first, otherwise as made) then gives a head's items to one XCD
+      const int64_t n_rows = (int64_t)n * G;
+      for (int64_t rb = 0; rb < n_rows; rb += rows_per) {
+        const int32_t in_block = (int32_t)std::min<int64_t>(rows_per, n_rows - rb);
+        const int32_t qmin = (int32_t)(rb / G), qmax = (int32_t)((rb + in_block - 1) / G);
+        // keys up to the group's first position are visible to every row:
+        // that part of the chunk (whole 32-key steps) needs no mask
+        const int32_t open = std::min(qmax + 1, (qmin + 1) / 32 * 32);
+        for (int g = 0; g < Hkv; ++g) {
           Proto pr;
-          pr.rows.assign(rows.begin() + rb, rows.begin() + std::min(rows.size(), rb + (size_t)rows_per));
-          int32_t qmin = n, qmax = 0;
-          for (auto& x : pr.rows) {
-            qmin = std::min(qmin, x.qpos);
-            qmax = std::max(qmax, x.qpos);
-          }
+          pr.row_begin = (int32_t)prefill_rows.size();
+          pr.n_rows = in_block;
+          for (int64_t x = rb; x < rb + in_block; ++x)
+            prefill_rows.push_back(Row{(int32_t)((tok0[r] + x / G) * Hq + g * G + x % G), (int32_t)(x / G), -1, -1});
+          pr.spans.reserve(prefix_spans.size() + 2);
           pr.spans = prefix_spans;
-          // keys up to the group's first position are visible to every row:
-          // that part of the chunk (whole 32-key steps) needs no mask
-          const int32_t open = std::min(std::min(n, qmax + 1), (qmin + 1) / 32 * 32);
           if (open > 0) pr.spans.push_back(Span{chunk_seg, 0, open, 0, 0, {0, 0, 0}});
-          if (std::min(n, qmax + 1) > open)
-            pr.spans.push_back(Span{chunk_seg, open, std::min(n, qmax + 1), 1, 0, {0, 0, 0}});
+          if (qmax + 1 > open) pr.spans.push_back(Span{chunk_seg, open, qmax + 1, 1, 0, {0, 0, 0}});
           pr.kv_head = g;
           pr.keys = prefix_keys + qmax + 1;
           pr.shared = false;
@@ -465,12 +578,70 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         }
       }
     }
+    // Few items leave most of the chip idle for as long as the longest takes:
+    // cut their keys into pieces, whose results a second launch merges.
+    std::vector<ItemSize> sizes(protos.size() / Hkv);   // of head 0's items
+    for (size_t i = 0; i < sizes.size(); ++i) {
+      int64_t n = 0;
+      for (const Span& sp : protos[i * Hkv].spans) n += ceil_div(sp.key_end - sp.key_begin, kKeysPerStep);
+      sizes[i] = ItemSize{(int32_t)std::min<int64_t>(n, std::numeric_limits<int32_t>::max()), protos[i * Hkv].n_rows};
+    }
+    const PieceCut cut = (wide && !plan->small_wide) || (!wide && p.kv_dtype == HALO_BF16)
+                             ? PieceCut{}
+                             : choose_pieces(sizes, Hkv, p.head_dim, wide);
+    if (cut.length > 0) {
+      whole.swap(protos);
+      protos.reserve(2 * whole.size());
+      std::vector<int32_t> ends;
+      for (size_t i = 0; i < whole.size(); i += Hkv) {
+        cut.ends(sizes[i / Hkv].steps, ends);
+        for (size_t k = 0; k < ends.size(); ++k)
+          for (int g = 0; g < Hkv; ++g) {
+            const Proto& w = whole[i + g];
+            if (ends.size() == 1) {
+              protos.push_back(w);
+              continue;
+            }
+            Proto pr;
+            pr.row_begin = w.row_begin;
+            pr.n_rows = w.n_rows;
+            pr.kv_head = w.kv_head;
+            pr.shared = false;
+            pr.wide = w.wide;
+            pr.part_at = (int32_t)(merge_bases.size() + g * ends.size() + k);
+            pr.keys = 0;
+            int64_t at = 0;   // first step of a span
+            const int64_t lo = k ? ends[k - 1] : 0, hi = ends[k];
+            for (const Span& sp : w.spans) {
+              const int64_t n = ceil_div(sp.key_end - sp.key_begin, kKeysPerStep);
+              const int64_t a = std::max(lo, at), b = std::min(hi, at + n);
+              if (a < b) {
+                Span piece = sp;
+                piece.key_begin = (int32_t)(sp.key_begin + (a - at) * kKeysPerStep);
+                piece.key_end = (int32_t)std::min<int64_t>(sp.key_end, sp.key_begin + (b - at) * kKeysPerStep);
+                pr.keys += paged(piece.key_end - piece.key_begin);
+                pr.spans.push_back(piece);
+              }
+              at += n;
+            }
+            protos.push_back(std::move(pr));
+          }
+        if (ends.size() > 1)
+          for (int g = 0; g < Hkv; ++g) {
+            merge_items.push_back(MergeItem{whole[i + g].row_begin, whole[i + g].n_rows, (int32_t)merge_bases.size(),
+                                            (int32_t)ends.size()});
+            merge_bases.resize(merge_bases.size() + ends.size());
+            plan->merge_item_rows = std::max(plan->merge_item_rows, whole[i + g].n_rows);
+            plan->merged_rows += whole[i + g].n_rows;
+          }
+      }
+    }
   }
 
   // Parts per output row; items whose rows all have a single part write
   // their final result directly.
   auto& n_parts = scratch<std::vector<int32_t>, 1>();
-  n_parts.assign(n_q_rows * Hq, 0);
+  n_parts.assign(prefill ? 0 : n_q_rows * Hq, 0);
   for (auto& pr : protos)
     for (auto& row : pr.rows) n_parts[row.q_row]++;
   // Rows that see no key at all get an item with no spans, which writes
@@ -496,7 +667,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   for (size_t i = 0; i < protos.size(); ++i) {
     bool all_one = true;
     for (auto& row : protos[i].rows) all_one &= (n_parts[row.q_row] == 1);
-    is_final[i] = prefill || all_one;
+    is_final[i] = prefill ? protos[i].part_at < 0 : all_one;
   }
 
   // Shared items first, then private ones; longest first within each class
@@ -537,6 +708,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   auto& item_chunk = scratch<std::vector<int32_t>, 2>();   // per narrow item: its proto's chunk id
   auto& spans = scratch<std::vector<Span>, 0>();
   auto& rows = scratch<std::vector<Row>, 0>();
+  if (prefill) rows.swap(prefill_rows);
   // Partial rows of each output row, in item order (CSR over q rows).
   auto& parts_indptr = scratch<std::vector<int32_t>, 3>();
   auto& parts_of = scratch<std::vector<int32_t>, 4>();
@@ -565,28 +737,30 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   auto& parts_fill = scratch<std::vector<int32_t>, 5>();
   parts_fill.assign(prefill ? 0 : n_q_rows * Hq, 0);
   int64_t part_rows = 0;
-  for (size_t oi : order) {
-    Proto& pr = protos[oi];
+  // One proto as an item: appended to `wide_out` or to `out` and `chunk_out`.
+  auto emit = [&](const Proto& pr, bool final_item, std::vector<Item>& out, std::vector<int32_t>& chunk_out,
+                  std::vector<Item>& wide_out) {
     Item it{};
-    it.row_begin = (int32_t)rows.size();
-    it.n_rows = (int32_t)pr.rows.size();
+    it.row_begin = prefill ? pr.row_begin : (int32_t)rows.size();
+    it.n_rows = prefill ? pr.n_rows : (int32_t)pr.rows.size();
     it.span_begin = (int32_t)spans.size();
     it.kv_head = pr.kv_head;
     it.keys = (int32_t)std::min<int64_t>(pr.keys, std::numeric_limits<int32_t>::max());
     // Private keys of a decode item are read by no other item: stream them
     // past the caches.
     it.flags = (!prefill && !pr.shared && !pr.wide) ? kItemStream : 0;
-    if (is_final[oi]) {
+    if (final_item) {
       it.part_base = -1;
     } else {
-      if (part_rows + it.n_rows > (int64_t)std::numeric_limits<int32_t>::max()) {
-        delete plan;
-        return fail(HALO_ERR_INVALID_ARGUMENT, "too many partial rows");
-      }
-      it.part_base = (int32_t)part_rows;
-      for (int i = 0; i < it.n_rows; ++i) {
-        const int32_t q = pr.rows[i].q_row;
-        parts_of[parts_indptr[q] + parts_fill[q]++] = (int32_t)(part_rows + i);
+      it.part_base = (int32_t)part_rows;   // (checked against the int32 range below)
+      if (prefill) {
+        merge_bases[pr.part_at] = it.part_base;
+        it.flags |= kItemPiece;
+      } else {
+        for (int i = 0; i < it.n_rows; ++i) {
+          const int32_t q = pr.rows[i].q_row;
+          parts_of[parts_indptr[q] + parts_fill[q]++] = (int32_t)(part_rows + i);
+        }
       }
       part_rows += it.n_rows;
     }
@@ -625,9 +799,22 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       it.s0_key_end = s0.key_end;
       it.s0_causal = s0.causal;
     }
-    (pr.wide ? witems : items).push_back(it);
-    if (!pr.wide) item_chunk.push_back(pr.chunk);
+    (pr.wide ? wide_out : out).push_back(it);
+    if (!pr.wide) chunk_out.push_back(pr.chunk);
+  };
+  for (size_t oi : order) {
+    const int64_t n = prefill ? protos[oi].n_rows : (int64_t)protos[oi].rows.size();
+    if (!is_final[oi] && part_rows + n > (int64_t)std::numeric_limits<int32_t>::max()) {
+      delete plan;
+      return fail(HALO_ERR_INVALID_ARGUMENT, "too many partial rows");
+    }
+    emit(protos[oi], is_final[oi], items, item_chunk, witems);
   }
+  auto& whole_items = scratch<std::vector<Item>, 4>();
+  auto& whole_witems = scratch<std::vector<Item>, 5>();
+  std::vector<int32_t> whole_chunk;
+  std::stable_sort(whole.begin(), whole.end(), [](const Proto& a, const Proto& b) { return a.keys > b.keys; });
+  for (const Proto& pr : whole) emit(pr, true, whole_items, whole_chunk, whole_witems);
 
   // Merge list: every decode row no final item writes, i.e. every row with
   // partial results (several, or one from an item that also holds
@@ -644,7 +831,9 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   merge_indptr.push_back(0);
   int64_t n_slots = 0;
   int32_t merge_k0 = 0;
-  if (!prefill) {
+  if (prefill) {
+    n_slots = part_rows;
+  } else {
     auto& merge_of = scratch<std::vector<int32_t>, 9>();
     merge_of.assign(n_q_rows * Hq, -1);
     auto& slot_of_part = scratch<std::vector<int32_t>, 10>();
@@ -703,18 +892,20 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   //    longest first and fill the open workgroup of their XCD (shared) or
   //    of the XCD with the fewest items (private). Workgroups then launch
   //    longest first, and the short ones fill the tail.
-  auto& recs = scratch<std::vector<ItemRec>, 0>();
-  const int64_t n_real_items = (int64_t)items.size();
-  if (!items.empty()) {
+  // Returns the number of workgroups, items and recs in slot order; -1 with
+  // the error set.
+  auto deal = [&](std::vector<Item>& items, const std::vector<int32_t>& item_chunk, size_t n_wide,
+                  std::vector<ItemRec>& recs) -> int64_t {
+    if (items.empty()) return 0;
     const int waves = narrow_items_per_block(p.kv_dtype);
     const int64_t n = (int64_t)items.size();
     const int slots = waves;
     const int cap = opt.items_per_block > 0 ? std::min(opt.items_per_block, slots) : slots;
     if (n > (int64_t)std::numeric_limits<int32_t>::max() / 2) {
-      delete plan;
-      return fail(HALO_ERR_INVALID_ARGUMENT, "too many narrow work items");
+      fail(HALO_ERR_INVALID_ARGUMENT, "too many narrow work items");
+      return -1;
     }
-    const bool rounds = (int64_t)witems.size() + (n + cap - 1) / cap > kNumCUs;
+    const bool rounds = (int64_t)n_wide + (n + cap - 1) / cap > kNumCUs;
     int64_t nb = std::max<int64_t>((n + cap - 1) / cap, std::min<int64_t>(n, kNumCUs));
     nb = (nb + 7) / 8 * 8;
     const int shared_unit = std::min(cap, opt.shared_unit > 0 ? opt.shared_unit : 4);
@@ -758,8 +949,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         for (size_t j = 0; j < xb[x].size(); ++j) blk[j * 8 + x].swap(xb[x][j]);
     }
     if (nb * slots > (int64_t)std::numeric_limits<int32_t>::max()) {
-      delete plan;
-      return fail(HALO_ERR_INVALID_ARGUMENT, "too many narrow work items");
+      fail(HALO_ERR_INVALID_ARGUMENT, "too many narrow work items");
+      return -1;
     }
     // one round: one min-heap of (load, block) per XCD over the blocks with
     // room left
@@ -804,8 +995,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       for (int32_t k = 0; k < u.count; ++k) {
         const int y = least_loaded_xcd();
         if (y < 0 || !place_on(y, u.first + k, 1, cost_of(items[u.first + k]))) {
-          delete plan;
-          return fail(HALO_ERR_INVALID_ARGUMENT, "internal: narrow items do not fit their workgroups");
+          fail(HALO_ERR_INVALID_ARGUMENT, "internal: narrow items do not fit their workgroups");
+          return -1;
         }
       }
     }
@@ -821,7 +1012,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         ItemRec& rc = recs[at];
         for (int r = 0; r < 16; ++r) {
           rc.q_row[r] = r < it.n_rows ? rows[it.row_begin + r].q_row : -1;
-          rc.aux[r] = r >= it.n_rows ? 0 : it.part_base >= 0 ? rows[it.row_begin + r].slot
+          rc.aux[r] = r >= it.n_rows ? 0 : !prefill && it.part_base >= 0 ? rows[it.row_begin + r].slot
                                                              : rows[it.row_begin + r].qpos;
         }
         if (it.n_spans > 0) {
@@ -831,9 +1022,22 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         }
       }
     items.swap(dealt);
-    plan->n_narrow_blocks = (int32_t)nb;
     plan->narrow_slots = slots;
+    return nb;
+  };
+  auto& recs = scratch<std::vector<ItemRec>, 0>();
+  auto& whole_recs = scratch<std::vector<ItemRec>, 1>();
+  const int64_t n_real_items = (int64_t)items.size();
+  const int64_t nb_main = deal(items, item_chunk, witems.size(), recs);
+  const int64_t nb_whole = nb_main < 0 ? -1 : deal(whole_items, whole_chunk, whole_witems.size(), whole_recs);
+  if (nb_whole < 0) {
+    delete plan;
+    return HALO_ERR_INVALID_ARGUMENT;
   }
+  plan->n_narrow_blocks = (int32_t)nb_main;
+  plan->n_whole_blocks = (int32_t)nb_whole;
+  plan->n_whole_wide = (int32_t)whole_witems.size();
+  plan->n_merge_items = (int32_t)merge_items.size();
   plan->n_items = (int32_t)n_real_items;
   plan->n_wide = (int32_t)witems.size();
   if (plan->n_wide == 0) plan->wide_rb = 0;
@@ -846,7 +1050,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   plan->merge_k0 = merge_k0;
   const size_t D = (size_t)p.head_dim;
   // partial O rows in the output element type, then one fp32 LSE per row
-  const int64_t part_elem = p.out_dtype == HALO_F32 ? 4 : 2;
+  // (a prefill's pieces: in fp32)
+  const int64_t part_elem = prefill || p.out_dtype == HALO_F32 ? 4 : 2;
   plan->workspace_bytes =
       n_slots ? align_up(n_slots * D * part_elem, 256) + align_up(n_slots * sizeof(float), 256) : 0;
 
@@ -871,6 +1076,11 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   L.merge_rows = place(sizeof(int32_t) * std::max<size_t>(merge_rows.size(), 1));
   L.merge_indptr = place(sizeof(int32_t) * merge_indptr.size());
   L.merge_parts = place(sizeof(int32_t) * std::max<size_t>(merge_parts.size(), 1));
+  L.merge_items = place(sizeof(MergeItem) * merge_items.size());
+  L.merge_bases = place(sizeof(int32_t) * merge_bases.size());
+  L.whole_items = place(sizeof(Item) * whole_items.size());
+  L.whole_recs = place(sizeof(ItemRec) * whole_recs.size());
+  L.whole_wide = place(sizeof(Item) * whole_witems.size());
   L.total = off;
   plan->layout = L;
   // (the image is not zero-filled first: each array is copied in and the
@@ -895,6 +1105,11 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         {L.merge_rows, merge_rows.data(), sizeof(int32_t) * merge_rows.size()},
         {L.merge_indptr, merge_indptr.data(), sizeof(int32_t) * merge_indptr.size()},
         {L.merge_parts, merge_parts.data(), sizeof(int32_t) * merge_parts.size()},
+        {L.merge_items, merge_items.data(), sizeof(MergeItem) * merge_items.size()},
+        {L.merge_bases, merge_bases.data(), sizeof(int32_t) * merge_bases.size()},
+        {L.whole_items, whole_items.data(), sizeof(Item) * whole_items.size()},
+        {L.whole_recs, whole_recs.data(), sizeof(ItemRec) * whole_recs.size()},
+        {L.whole_wide, whole_witems.data(), sizeof(Item) * whole_witems.size()},
     };
     const size_t n = sizeof(parts) / sizeof(parts[0]);
     for (size_t i = 0; i < n; ++i) {
@@ -982,7 +1197,7 @@ extern "C" halo_status_t halo_plan_get_stats(const halo_plan_t* plan, halo_plan_
   st->num_wide_items = plan->n_wide;
   st->wide_row_blocks = plan->wide_rb;
   st->num_shared_items = plan->n_shared_items;
-  st->num_merge_rows = plan->n_merge;
+  st->num_merge_rows = plan->prefill ? (int32_t)plan->merged_rows : plan->n_merge;
   st->num_partial_rows = plan->n_part_rows;
   st->num_query_rows = plan->num_query_rows;
   st->distinct_kv_tokens = plan->distinct_kv_tokens;

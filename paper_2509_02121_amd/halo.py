@@ -456,7 +456,7 @@ def _check_run(plan, device_meta, q, k_pool, v_pool, o, lse, workspace, library_
         if have < n:
             raise ValueError(f"{name} has {have} {unit}, the plan needs at least {n}")
     ws = _nbytes(workspace) if workspace is not None else 0
-    if not library_workspace and ws < plan.workspace_bytes:
+    if not library_workspace and not plan.is_prefill and ws < plan.workspace_bytes:
         raise ValueError(f"workspace has {ws} bytes, the plan needs {plan.workspace_bytes}")
     _gpu(device_meta, "device_meta")
     _gpu(q, "q", kv)
@@ -694,7 +694,10 @@ class PrefixAttention:
         self._metas = [self._meta_buffer(self.plan.device_meta_bytes), None]
         self._cur = 0
         self.workspace = (torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
-                          if self.plan.workspace_bytes else None)
+                          if self.plan.workspace_bytes and not self.plan.is_prefill else None)
+        # a prefill's workspace, one per stream: its calls may overlap on
+        # several streams
+        self._prefill_ws = {}
         self._copy_stream = torch.cuda.Stream(device=self.device)
         # runs that read buffer i since its last upload: an event after the
         # last run() per stream, and the streams of bound callables (whose
@@ -754,7 +757,7 @@ class PrefixAttention:
         if not applied:
             self.plan = Plan.from_csr(self.plan.params, csr, self.options)
             ws_have = self.workspace.numel() if self.workspace is not None else 0
-            if self.plan.workspace_bytes > ws_have:
+            if not self.plan.is_prefill and self.plan.workspace_bytes > ws_have:
                 # runs in flight may still use the old workspace
                 torch.cuda.synchronize(self.device)
                 self.workspace = torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
@@ -782,6 +785,26 @@ class PrefixAttention:
         ev.record(s)
         self._runs[self._cur][s] = ev
 
+    def _workspace_on(self, stream):
+        """The workspace of a call on `stream` (None: the current stream).
+        Decode: this object's own. Prefill: the stream's, or, while the
+        stream is being captured, a new one from the graph's own pool."""
+        import torch
+        if not self.plan.is_prefill:
+            return self.workspace
+        if not self.plan.workspace_bytes:
+            return None
+        s = stream if stream is not None else torch.cuda.current_stream(self.device)
+        ws = self._prefill_ws.get(s.cuda_stream)
+        with torch.cuda.stream(s):
+            if torch.cuda.is_current_stream_capturing():
+                return torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
+            if ws is None or ws.numel() < self.plan.workspace_bytes:
+                # (a smaller one goes back to this stream's memory, in order)
+                ws = torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
+                self._prefill_ws[s.cuda_stream] = ws
+        return ws
+
     def alloc_outputs(self, q):
         import torch
         o = torch.empty(q.shape, dtype=self.out_dtype, device=q.device)
@@ -793,7 +816,7 @@ class PrefixAttention:
         lse) with every pointer converted once (for tight timing loops).
         The tensors must stay alive while the callable is used."""
         fn = _LIB.halo_prefix_attn_prefill if self.plan.is_prefill else _LIB.halo_prefix_attn_decode
-        ws = self.workspace
+        ws = self._workspace_on(stream)
         _check_run(self.plan, self.meta, q, k_pool, v_pool, o, lse, ws)
         self._bound[self._cur].add(self._before_run(stream))
         args = (self.plan._handle, self.meta.data_ptr(), q.data_ptr(), k_pool.data_ptr(),
@@ -801,7 +824,7 @@ class PrefixAttention:
                 ws.data_ptr() if ws is not None else None,
                 ws.numel() if ws is not None else 0, _stream_handle(stream))
 
-        def call():
+        def call(_workspace=ws):   # (kept alive by the callable)
             st = fn(*args)
             if st != HALO_OK:
                 _check(st)
@@ -813,6 +836,6 @@ class PrefixAttention:
             lse = lse if lse is not None else lse_new
         fn = prefix_attn_prefill if self.plan.is_prefill else prefix_attn_decode
         s = self._before_run(stream)
-        fn(self.plan, self.meta, q, k_pool, v_pool, o, lse, self.workspace, stream)
+        fn(self.plan, self.meta, q, k_pool, v_pool, o, lse, self._workspace_on(stream), stream)
         self._after_run(s)
         return o, lse

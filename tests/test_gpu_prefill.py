@@ -37,3 +37,59 @@ def test_row_blocks_of_prefill_items(gpu_lib, d, out_dtype, options):
     ro, rl, rows = oracle_for(w)
     assert_parity(w, o, lse, ro, rl, rows, f"row blocks d{d} {options}")
     assert np.isfinite(o).all()
+
+
+@pytest.mark.parametrize("dtype,d,out_dtype", [(torch.bfloat16, 128, torch.bfloat16), (torch.bfloat16, 64, torch.float32),
+                                               (torch.float32, 128, torch.float32), (torch.float32, 64, torch.float32)])
+@pytest.mark.parametrize("prefix,q_len", [(3001, [70]), (1500, [1, 200, 33]), (0, [900]), (7000, [1])])
+def test_items_cut_into_pieces(gpu_lib, dtype, d, out_dtype, prefix, q_len):
+    """Few items with many keys: their keys are cut into pieces (inside cached
+    segments and inside the causal chunk, where some rows of a piece see no
+    key) and merged; without the workspace the items run uncut."""
+    print(f"case: prefill pieces {dtype} d{d} prefix {prefix} chunks {q_len}", flush=True)
+    seg_len = [prefix // 3, prefix - prefix // 3] + q_len
+    paths = [[0, 1, 2 + i] for i in range(len(q_len))]
+    w = build_workload("pieces", 72, 6, 2, d, dtype, seg_len, paths, q_len,
+                       value_scale=0.5 if dtype == torch.bfloat16 else 1.0)
+    o, lse, pa = _run(w, None, out_dtype)
+    assert pa.plan.workspace_bytes > 0 and pa.plan.stats()["num_merge_rows"] > 0, "the items are cut"
+    ro, rl, rows = oracle_for(w)
+    assert_parity(w, o, lse, ro, rl, rows, "pieces")
+    o2, lse2 = pa.alloc_outputs(w.q)
+    halo.prefix_attn_prefill(pa.plan, pa.meta, w.q, w.k_pool, w.v_pool, o2, lse2, None)
+    torch.cuda.synchronize()
+    assert_parity(w, o2.double().cpu().numpy(), lse2.double().cpu().numpy(), ro, rl, rows, "uncut")
+
+
+def test_piecewise_prefill_on_two_streams_and_in_a_graph(gpu_lib):
+    """Calls of one object that overlap on two streams have a workspace each,
+    and a captured call replays with the eager call's bits."""
+    print("case: prefill pieces on two streams, captured", flush=True)
+    w = to_device(build_workload("streams", 73, 8, 2, 128, torch.bfloat16, [5000, 150], [[0, 1]], [150],
+                                 value_scale=0.5))
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    assert pa.plan.workspace_bytes > 0
+    want, want_lse = pa.run(w.q, w.k_pool, w.v_pool)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [pa.alloc_outputs(w.q) for _ in streams]
+    for _ in range(20):
+        for s, (o, lse) in zip(streams, outs):
+            pa.run(w.q, w.k_pool, w.v_pool, o, lse, stream=s)
+    torch.cuda.synchronize()
+    o, lse = pa.alloc_outputs(w.q)
+    side = torch.cuda.Stream()
+    call = pa.bind(w.q, w.k_pool, w.v_pool, o, lse, side)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for _ in range(3):
+        o.zero_()
+        graph.replay()
+        pa.run(w.q, w.k_pool, w.v_pool)   # eager work between the replays
+        torch.cuda.synchronize()
+        assert torch.equal(o, want) and torch.equal(lse, want_lse)
+    for o, lse in outs:
+        assert torch.equal(o, want) and torch.equal(lse, want_lse)
