@@ -1117,6 +1117,7 @@ struct MergeArgs {
   float* lse;
   int32_t n_merge;
   int32_t k0;   // partials of entry r at slots k * n_merge + r for k < k0
+  int32_t n_parts;
 };
 
 // Rows per merge workgroup (256 threads, 16 bytes of a row per thread).
@@ -1223,6 +1224,115 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void m
   if (t == 0 && a.lse) a.lse[q_row] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : kNegInf;
 }
 
+// Few rows of many partials: a workgroup merges one row, by the same rule. Its
+// groups of TPR threads take every kGroups-th partial each; a wave's groups are
+// then combined by lane exchanges and the four waves through LDS. The other
+// merge kernels walk a row's partials in rounds of 8 of two dependent loads
+// each: 4 requests of 12000-24000 private keys (128 rows of 24-47 partials)
+// 58.3 -> 53.3 us, one of 24000 33 -> 20 us (whole calls, 32/8 heads, d 128).
+// TP: the partials' element type; slot_of(k): the slot of partial k < n.
+template <int D, typename TP, typename TO, typename SlotOf>
+__device__ __forceinline__ void merge_row(const void* part_o, const float* part_lse, int n, SlotOf slot_of, TO* o,
+                                          float* lse, int64_t q_row) {
+  constexpr int E = 16 / (int)sizeof(TP);
+  constexpr int TPR = D / E;
+  constexpr int kGroups = 256 / TPR;
+  constexpr int kBatch = 4;   // partials of a group in flight
+  __shared__ float part_acc[4][D];
+  __shared__ float part_m[4], part_w[4];
+  const int t = threadIdx.x % TPR, g = threadIdx.x / TPR;
+  const int wave = threadIdx.x >> 6;
+  float m = kNegInf, wsum = 0.f;
+  float acc[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] = 0.f;
+  // this thread's running sums, scaled to the maximum m_new
+  auto rescale = [&](float m_new) {
+    const float alpha = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+    wsum *= alpha;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] *= alpha;
+    m = m_new;
+  };
+  for (int k0 = g; k0 < n; k0 += kBatch * kGroups) {
+    float l[kBatch];
+    u32x4_t raw[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int k = k0 + j * kGroups;
+      l[j] = kNegInf;
+      raw[j] = u32x4_t{0u, 0u, 0u, 0u};
+      if (k < n) {
+        const int64_t slot = slot_of(k);
+        l[j] = part_lse[slot];
+        raw[j] = *reinterpret_cast<const u32x4_t*>(static_cast<const TP*>(part_o) + slot * D + E * t);
+      }
+    }
+    float m_new = m;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) m_new = fmaxf(m_new, l[j]);
+    if (m_new == kNegInf) continue;
+    rescale(m_new);
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const float w = __builtin_amdgcn_exp2f(l[j] - m);   // 0 for an absent partial
+      float v[E];
+      unpack16<TP, E>(raw[j], v);
+      wsum += w;
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] = __builtin_fmaf(w, v[e], acc[e]);
+    }
+  }
+  // over the groups of the wave
+  float m_wave = m;
+#pragma unroll
+  for (int x = TPR; x < 64; x <<= 1) m_wave = fmaxf(m_wave, __shfl_xor(m_wave, x));
+  if (m_wave != kNegInf) rescale(m_wave);
+#pragma unroll
+  for (int x = TPR; x < 64; x <<= 1) {
+    wsum += __shfl_xor(wsum, x);
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] += __shfl_xor(acc[e], x);
+  }
+  if ((threadIdx.x & 63) < TPR) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) part_acc[wave][E * t + e] = acc[e];
+    if (t == 0) {
+      part_m[wave] = m_wave;
+      part_w[wave] = wsum;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= D / 4) return;
+  // 4 dims per thread
+  float mx = kNegInf;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) mx = fmaxf(mx, part_m[w]);
+  const float m_use = mx == kNegInf ? 0.f : mx;
+  float sum = 0.f;
+  f32x4_t out = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float x = __builtin_amdgcn_exp2f(part_m[w] - m_use);
+    sum += x * part_w[w];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = __builtin_fmaf(x, part_acc[w][4 * threadIdx.x + e], out[e]);
+  }
+  store4(o + q_row * D + 4 * threadIdx.x, out * (sum > 0.f ? 1.f / sum : 0.f));
+  if (threadIdx.x == 0 && lse) lse[q_row] = sum > 0.f ? (mx + __log2f(sum)) * kLn2 : kNegInf;
+}
+
+// Merge entry blockIdx.x (see merge_kernel for the slots).
+template <int D, typename TO>
+__global__ __launch_bounds__(256) void merge_row_kernel(MergeArgs a) {
+  const int r = blockIdx.x;
+  const int p0 = a.merge_indptr[r], n = a.merge_indptr[r + 1] - p0;
+  merge_row<D, TO, TO>(
+      a.part_o, a.part_lse, n,
+      [&](int k) { return k < a.k0 ? (int64_t)k * a.n_merge + r : (int64_t)a.merge_parts[p0 + k]; },
+      static_cast<TO*>(a.o), a.lse, a.merge_rows[r]);
+}
+
 // The rows of prefill items whose keys were cut into pieces, by the same rule.
 // A piece's partials are contiguous (row k of the item at its part_base + k,
 // fp32), so a row's are found from the item's list of bases: one group of D / 4
@@ -1285,6 +1395,17 @@ __global__ __launch_bounds__(256) void merge_items_kernel(MergeItemArgs a) {
   if (t == 0 && a.lse) a.lse[q_row] = wsum > 0.f ? (mx + __log2f(wsum)) * kLn2 : kNegInf;
 }
 
+// Row blockIdx.x % blocks_per_item of prefill item blockIdx.x / blocks_per_item.
+template <int D, typename TO>
+__global__ __launch_bounds__(256) void merge_item_row_kernel(MergeItemArgs a) {
+  const MergeItem mi = a.items[blockIdx.x / a.blocks_per_item];
+  const int r = blockIdx.x % a.blocks_per_item;
+  if (r >= mi.n_rows) return;
+  merge_row<D, float, TO>(
+      a.part_o, a.part_lse, mi.n_parts, [&](int k) { return (int64_t)a.bases[mi.part_begin + k] + r; },
+      static_cast<TO*>(a.o), a.lse, a.rows[mi.row_begin + r].q_row);
+}
+
 // ---------------------------------------------------------------- host side
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -1302,6 +1423,12 @@ int pad_to(int n, int m) { return (n + m - 1) / m * m; }
 // Share (percent) of the narrow rounds interleaved with the wide ones; the
 // rest run after the last wide round.
 constexpr int kWideSpanNarrowPct = 80;
+
+// A workgroup merges one row where there are more than kMergeK0 partials per
+// row (fewer take one round anyway) and at most kMergeRowMax rows: two rounds
+// of workgroups on the chip (1024 rows of 10 partials: 103 us both ways; 2048
+// of 31: 194.5 -> 192.7 us; 256 of 15: 24.1 -> 22.5 us; whole calls).
+constexpr int kMergeRowMax = 4096;
 
 int lcm_int(int a, int b) {
   int x = a, y = b;
@@ -1338,7 +1465,9 @@ void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, bool s
       hipLaunchKernelGGL((attn_kernel<T, D, TO, 0>), dim3(grid), dim3(64 * W), 0, stream, args);
     }
   }
-  if (margs.n_merge > 0) {
+  if (margs.n_merge > 0 && margs.n_merge <= kMergeRowMax && margs.n_parts > kMergeK0 * (int64_t)margs.n_merge) {
+    hipLaunchKernelGGL((merge_row_kernel<D, TO>), dim3(margs.n_merge), dim3(256), 0, stream, margs);
+  } else if (margs.n_merge > 0) {
     constexpr int rpb = merge_rows_per_block<D, TO>();
     const int blocks = (margs.n_merge + rpb - 1) / rpb;
     hipLaunchKernelGGL((merge_kernel<D, TO>), dim3(blocks), dim3(256), 0, stream, margs);
@@ -1346,7 +1475,13 @@ void launch_attention(AttnArgs args, const MergeArgs& margs, int wide_rb, bool s
 }
 
 template <int D, typename TO>
-void launch_merge_items(MergeItemArgs args, int n_items, int most_rows, hipStream_t stream) {
+void launch_merge_items(MergeItemArgs args, int n_items, int most_rows, int64_t rows, int64_t parts,
+                        hipStream_t stream) {
+  if (rows <= kMergeRowMax && parts > kMergeK0 * rows) {
+    args.blocks_per_item = most_rows;
+    hipLaunchKernelGGL((merge_item_row_kernel<D, TO>), dim3(n_items * most_rows), dim3(256), 0, stream, args);
+    return;
+  }
   constexpr int rpb = 256 / (D / 4);
   args.blocks_per_item = (most_rows + rpb - 1) / rpb;
   hipLaunchKernelGGL((merge_items_kernel<D, TO>), dim3(n_items * args.blocks_per_item), dim3(256), 0, stream, args);
@@ -1403,7 +1538,7 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
                   reinterpret_cast<const int32_t*>(m + L.merge_rows),
                   reinterpret_cast<const int32_t*>(m + L.merge_indptr),
                   reinterpret_cast<const int32_t*>(m + L.merge_parts),
-                  o, lse, plan->n_merge, plan->merge_k0};
+                  o, lse, plan->n_merge, plan->merge_k0, plan->n_merge_parts};
   if (plan->n_narrow_blocks > 0 &&
       plan->narrow_slots != (p.kv_dtype == HALO_BF16 ? block_waves<__bf16>() : block_waves<float>()))
     return fail(HALO_ERR_INVALID_ARGUMENT, "internal: narrow slots per workgroup differ from its waves");
@@ -1427,13 +1562,14 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
                            reinterpret_cast<const MergeItem*>(m + L.merge_items),
                            reinterpret_cast<const int32_t*>(m + L.merge_bases),
                            reinterpret_cast<const Row*>(m + L.rows), o, lse, 0};
-    const int n = plan->n_merge_items, rows = plan->merge_item_rows;
+    const int n = plan->n_merge_items, most = plan->merge_item_rows;
+    const int64_t rows = plan->merged_rows, parts = plan->n_part_slots;
     if (D == 128) {
-      if (out_f32) launch_merge_items<128, float>(ma, n, rows, st);
-      else launch_merge_items<128, __bf16>(ma, n, rows, st);
+      if (out_f32) launch_merge_items<128, float>(ma, n, most, rows, parts, st);
+      else launch_merge_items<128, __bf16>(ma, n, most, rows, parts, st);
     } else {
-      if (out_f32) launch_merge_items<64, float>(ma, n, rows, st);
-      else launch_merge_items<64, __bf16>(ma, n, rows, st);
+      if (out_f32) launch_merge_items<64, float>(ma, n, most, rows, parts, st);
+      else launch_merge_items<64, __bf16>(ma, n, most, rows, parts, st);
     }
   }
   return hip_check("attention launch");
