@@ -396,7 +396,6 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   int32_t n_chunks = 0;
 
   if (!prefill) {
-    const int kc_shared = opt.kc_shared > 0 ? opt.kc_shared : 512;
     // Private chunks: the longest of 2048, 1024, 512 and 256 keys that
     // still leaves >= 3 items per CU (longer chunks write and merge fewer
     // partials; with fewer items a CU has too few loads in flight), else 256.
@@ -416,7 +415,6 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         kc_private_default = kc;
         break;
       }
-    const int kc_private = opt.kc_private > 0 ? opt.kc_private : kc_private_default;
     for (int r = 0; r < R; ++r) {
       int64_t keys = 0;
       for (int32_t i = path_begin(r); i < path_end(r); ++i) keys += f.seg_len[f.req_seg_ids[i]];
@@ -445,6 +443,42 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       }
     const bool wide = p.kv_dtype == HALO_BF16 &&
                       (opt.wide == 1 || (opt.wide == -1 && shared_work >= 16.0 * (1 << 20)));
+    // Shared chunks of 512 keys; shorter where the batch is small. An item is
+    // one wave's chain of 32-key steps (0.6 us each for bf16 at d = 128, 2.4
+    // for fp32), so few long items keep a small call waiting: 256 keys while
+    // the whole batch is at most 4 items per CU, and, while its K and V are so
+    // few bytes that HBM is not what holds it, shared and private ones the
+    // shortest that leaves at most 960 items (beyond, starts and partials cost
+    // more than the shorter chains save). Measured (us, at 512 / 256 keys and
+    // as chosen): 8 requests on 256 shared keys (fp32, d 64) 15.4 -> 8.1; 4 on
+    // 1000 15.7 -> 8.3; 16 on 2000 16.4 -> 10.8, fp32 on 1000 48.9 -> 18; 32 on
+    // 2000 16.7 -> 13.6. Past the limits it turns: 64 on 2048 (1368 items) 21.5,
+    // at 256 keys (1880) 25.6; 16 requests of 500-1500 private keys (67 MB, 584
+    // items) 13.8, at 128 keys 15.1.
+    int kc_shared = 512;
+    int kc_private = kc_private_default;
+    if (!wide) {
+      auto all_items = [&](int64_t ks, int64_t kp) {
+        int64_t n = private_items(kp) * ceil_div(G, kRowsPerItem);
+        for (int s = 0; s < S; ++s)
+          if (refs[s] >= 2)
+            n += ceil_div(paged(f.seg_len[s]), ks) * ceil_div((int64_t)refs[s] * G, kRowsPerItem) * Hkv;
+        return n;
+      };
+      constexpr int64_t kLatencyBytes = 60 << 20, kMaxShortItems = 960;
+      int64_t tokens = 0;
+      for (int s = 0; s < S; ++s) tokens += refs[s] ? paged(f.seg_len[s]) : 0;
+      const int64_t bytes = tokens * 2 * Hkv * p.head_dim * (p.kv_dtype == HALO_BF16 ? 2 : 4);
+      if (all_items(256, kc_private) <= 4 * kNumCUs) kc_shared = 256;
+      if (kc_private == 256 && bytes <= kLatencyBytes)
+        for (int kc : {64, 96, 128, 192})
+          if (all_items(kc, kc) <= kMaxShortItems) {
+            kc_shared = kc_private = kc;
+            break;
+          }
+    }
+    if (opt.kc_shared > 0) kc_shared = opt.kc_shared;
+    if (opt.kc_private > 0) kc_private = opt.kc_private;
     int rows_per = kRowsPerItem;
     int kc = kc_shared;
     if (wide) {

@@ -1,0 +1,65 @@
+"""GPU parity of small decode batches: few rows of many partials (a merge
+workgroup per row) and the short key chunks that leave a small batch enough
+items, against the oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import assert_parity, oracle_for, run_library
+from paper_2509_02121_amd import halo
+from gpu_helpers import params_of
+from workloads import build_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d,out_dtype", [(torch.bfloat16, 128, torch.bfloat16), (torch.bfloat16, 64, torch.bfloat16),
+                                               (torch.bfloat16, 128, torch.float32), (torch.float32, 128, torch.float32),
+                                               (torch.float32, 64, torch.float32)])
+@pytest.mark.parametrize("keys", [520, 1088, 9000, 17000])
+def test_few_rows_of_many_partials(gpu_lib, dtype, d, out_dtype, keys):
+    """9 partials (one more than the fixed slots), as many as a row's groups of
+    threads take in one round and more, one request without private keys, and
+    one without any key beside them."""
+    print(f"case: many partials {dtype} d{d} {out_dtype} {keys} keys", flush=True)
+    seg_len = [70, keys, keys // 2 + 3]
+    paths = [[0, 1], [0, 2], [0], []]
+    w = build_workload("parts", 81, 6, 2, d, dtype, seg_len, paths, value_scale=0.5 if dtype == torch.bfloat16 else 1.0)
+    o, lse, pa = run_library(w, out_dtype)
+    m = pa.plan.inspect()
+    assert np.diff(m["merge_indptr"]).max() > 8
+    ro, rl, rows = oracle_for(w)
+    assert_parity(w, o, lse, ro, rl, rows, f"{keys} keys")
+
+
+@pytest.mark.parametrize("n_req,prefix,private,longest", [(1, 0, 500, 64), (4, 1000, 200, 64), (16, 2000, 170, 96),
+                                                          (32, 2000, 170, 256), (64, 2048, 290, 512)])
+def test_chunk_lengths_of_small_batches(gpu_lib, n_req, prefix, private, longest):
+    """The planner's key chunks shorten as the batch gets smaller (longest:
+    keys of the longest chunk), fresh and after growing in place."""
+    print(f"case: chunk lengths {n_req} requests", flush=True)
+    rng = np.random.default_rng(n_req)
+    own = [int(x) for x in rng.integers(private * 3 // 4, private * 5 // 4, size=n_req)]
+    seg_len = ([prefix] if prefix else []) + own
+    paths = [([0] if prefix else []) + [len(seg_len) - n_req + r] for r in range(n_req)]
+    w = build_workload("chunks", 82, 32, 8, 128, torch.bfloat16, seg_len, paths, value_scale=0.5)
+    o, lse, pa = run_library(w)
+    spans = pa.plan.inspect()["spans"]
+    assert (spans[:, 2] - spans[:, 1]).max() == longest
+    sample = list(range(0, n_req, max(1, n_req // 4)))
+    ro, rl, rows = oracle_for(w, sample)
+    assert_parity(w, o, lse, ro, rl, rows, "fresh")
+    # the plan of a shorter batch, grown in place to this one
+    grown = w.forest_csr()
+    short = {k: v.copy() for k, v in grown.items() if v is not None}
+    cut = np.array([0] * (1 if prefix else 0) + [int(rng.integers(0, 60)) for _ in own], np.int32)
+    short["seg_len"] = grown["seg_len"] - cut
+    pages = [w.seg_pages[s][:(int(n) + 15) // 16] for s, n in enumerate(short["seg_len"])]
+    short["seg_page_indptr"] = np.concatenate([[0], np.cumsum([len(p) for p in pages])]).astype(np.int32)
+    short["seg_page_ids"] = np.concatenate(pages).astype(np.int32)
+    pa = halo.PrefixAttention(params_of(w), short, "cuda")
+    assert pa.update(grown)
+    o, lse = pa.run(w.q, w.k_pool, w.v_pool)
+    torch.cuda.synchronize()
+    assert_parity(w, o.double().cpu().numpy(), lse.double().cpu().numpy(), ro, rl, rows, "grown")
