@@ -144,6 +144,9 @@ struct MetaLayout {
   size_t whole_items = 0;    // as items, item_recs and wide_items
   size_t whole_recs = 0;
   size_t whole_wide = 0;
+  // Room on the device for an update's patches (zero in the image).
+  size_t patches = 0;        // Patch [max_patches]
+  size_t max_patches = 0;
   size_t total = 0;
 };
 
@@ -175,11 +178,21 @@ struct DefaultInitAlloc : std::allocator<T> {
 // over segments: tail_span[tail_indptr[s] .. tail_indptr[s+1])), each with
 // the image byte offsets of the item whose first span it is and of that
 // item's lane record (-1 if none).
+// patches: every image word an update has written since the plan was made,
+// as it is now (rebuilt by each update; more than MetaLayout::max_patches:
+// incomplete, the sections are uploaded instead). touched: the
+// segments that ever changed; min_pages: the fewest pages each has had.
+struct Patch {
+  uint32_t word;   // offset in the image, in 32-bit words
+  int32_t value;
+};
 struct AppendIndex {
   std::vector<int32_t> seg_len, page_indptr, page_ids, req_indptr, req_ids, refs;
   std::vector<int32_t> page_slot_off, len_lo, len_hi;
   std::vector<int32_t> tail_indptr, tail_span;
   std::vector<int64_t> tail_item, tail_rec;
+  std::vector<Patch> patches;
+  std::vector<int32_t> touched, min_pages;   // min_pages: -1 until touched
 };
 
 }  // namespace halo

@@ -1578,6 +1578,14 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
 }  // namespace
 
 namespace {
+// An in-place update's changed words, written into the metadata image. The
+// words of a 70B-shaped decode step are 140 KB of patches where the sections
+// they lie in are 4 MB.
+__global__ __launch_bounds__(256) void patch_kernel(int32_t* image, const Patch* patches, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) image[patches[i].word] = patches[i].value;
+}
+
 halo_status_t upload_bytes(void* dst, const void* src, size_t n, hipStream_t stream) {
   hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, stream);
   if (e != hipSuccess) return fail(HALO_ERR_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
@@ -1593,7 +1601,7 @@ extern "C" halo_status_t halo_plan_upload(const halo_plan_t* plan, void* device_
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta needs " + std::to_string(plan->layout.total) + " bytes");
   if ((reinterpret_cast<uintptr_t>(device_meta) & 255) != 0)
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta must be 256-byte aligned");
-  return upload_bytes(device_meta, plan->meta.data(), plan->layout.total, static_cast<hipStream_t>(stream));
+  return upload_bytes(device_meta, plan->meta.data(), plan->layout.patches, static_cast<hipStream_t>(stream));
 }
 
 extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* device_meta,
@@ -1604,11 +1612,24 @@ extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* 
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta needs " + std::to_string(plan->layout.total) + " bytes");
   if ((reinterpret_cast<uintptr_t>(device_meta) & 255) != 0)
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta must be 256-byte aligned");
-  // The sections an in-place update rewrites lie between the segment
-  // length table and the row table, in that order in the image.
+  // The words an in-place update writes go as patches; where they would be
+  // more bytes than the sections they lie in (between the segment length table
+  // and the row table, in that order in the image), the sections go whole.
+  const std::vector<Patch>& patches = plan->append.patches;
   const size_t at = plan->layout.seg_len, end = plan->layout.rows;
-  return upload_bytes(static_cast<uint8_t*>(device_meta) + at, plan->meta.data() + at, end - at,
-                      static_cast<hipStream_t>(stream));
+  const hipStream_t st = static_cast<hipStream_t>(stream);
+  uint8_t* meta = static_cast<uint8_t*>(device_meta);
+  const size_t bytes = patches.size() * sizeof(Patch);
+  if (patches.size() > plan->layout.max_patches || bytes >= end - at)
+    return upload_bytes(meta + at, plan->meta.data() + at, end - at, st);
+  if (patches.empty()) return HALO_OK;
+  const halo_status_t rc = upload_bytes(meta + plan->layout.patches, patches.data(), bytes, st);
+  if (rc != HALO_OK) return rc;
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(patch_kernel, dim3((patches.size() + 255) / 256), dim3(256), 0, st,
+                     reinterpret_cast<int32_t*>(meta), reinterpret_cast<const Patch*>(meta + plan->layout.patches),
+                     (int)patches.size());
+  return hip_check("metadata patch launch");
 }
 
 extern "C" halo_status_t halo_prefix_attn_decode(const halo_plan_t* plan, const void* device_meta,

@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <functional>
 #include <limits>
@@ -1115,6 +1116,23 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   L.whole_items = place(sizeof(Item) * whole_items.size());
   L.whole_recs = place(sizeof(ItemRec) * whole_recs.size());
   L.whole_wide = place(sizeof(Item) * whole_witems.size());
+  // Room for the patches of the segments that can change: a length, the pages
+  // of the last spans and of the growth reserve, and per last span its end, the
+  // inline copy of it and the record's page ids.
+  if (!prefill) {
+    std::vector<size_t> pages(S, 0);
+    for (const Span& sp : spans)
+      if (refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg])
+        pages[sp.seg] = (size_t)(slot_off[sp.seg + 1] - slot_off[sp.seg]) - sp.key_begin / p.page_size;
+    for (int s = 0; s < S; ++s)
+      if (refs[s] < 2) L.max_patches += 1 + (refs[s] ? pages[s] : (size_t)(slot_off[s + 1] - slot_off[s]));
+    for (const Span& sp : spans)
+      if (refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg])
+        L.max_patches += 2 + std::min<size_t>(32, pages[sp.seg]);
+    // (an update that needs more uploads the sections whole)
+    L.max_patches = std::min(L.max_patches, (L.rows - L.seg_len) / 4 / sizeof(Patch));
+  }
+  L.patches = place(sizeof(Patch) * L.max_patches);
   L.total = off;
   plan->layout = L;
   // (the image is not zero-filled first: each array is copied in and the
@@ -1144,6 +1162,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         {L.whole_items, whole_items.data(), sizeof(Item) * whole_items.size()},
         {L.whole_recs, whole_recs.data(), sizeof(ItemRec) * whole_recs.size()},
         {L.whole_wide, whole_witems.data(), sizeof(Item) * whole_witems.size()},
+        {L.patches, nullptr, 0},
     };
     const size_t n = sizeof(parts) / sizeof(parts[0]);
     for (size_t i = 0; i < n; ++i) {
@@ -1207,6 +1226,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         ax.len_hi[s] = std::min(first_tail ? slots_end : ax.len_hi[s], clamp32((int64_t)sp.key_begin + cap));
       }
     }
+    ax.patches.reserve(L.max_patches + 1);   // one more says that they are too many
+    ax.min_pages.assign(S, -1);
   }
 
   *plan_out = plan;
@@ -1333,6 +1354,11 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
     const int32_t len = f.seg_len[s], old = mx.seg_len[s];
     if (len == old) continue;
     const int64_t np = ceil_div(len, ps), np_old = ceil_div(old, ps);
+    if (mx.min_pages[s] < 0) {
+      mx.touched.push_back(s);
+      mx.min_pages[s] = (int32_t)np_old;
+    }
+    mx.min_pages[s] = (int32_t)std::min<int64_t>(mx.min_pages[s], np);
     if (np > np_old)
       memcpy(slots + mx.page_slot_off[s] + np_old, f.seg_page_ids + f.seg_page_indptr[s] + np_old,
              sizeof(int32_t) * (np - np_old));
@@ -1351,6 +1377,28 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
     plan->distinct_kv_tokens += len - old;
     plan->visible_pairs += (int64_t)(len - old) * mx.refs[s] * plan->params.num_q_heads;
     mx.seg_len[s] = len;
+  }
+  // The patches: every word an update has written since the plan was made.
+  auto patch = [&](size_t byte) {
+    if (mx.patches.size() <= L.max_patches)
+      mx.patches.push_back(Patch{(uint32_t)(byte / 4), *reinterpret_cast<const int32_t*>(m + byte)});
+  };
+  mx.patches.clear();
+  for (int32_t s : mx.touched) {
+    if (mx.patches.size() > L.max_patches) break;
+    patch(L.seg_len + 4 * (size_t)s);
+    const int64_t np = ceil_div(mx.seg_len[s], ps), from = mx.min_pages[s];
+    for (int64_t j = from; j < np; ++j) patch(L.page_ids + 4 * (size_t)(mx.page_slot_off[s] + j));
+    for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
+      const size_t at = L.spans + sizeof(Span) * (size_t)mx.tail_span[k];
+      patch(at + offsetof(Span, key_end));
+      if (mx.tail_item[k] >= 0) patch((size_t)mx.tail_item[k] + offsetof(Item, s0_key_end));
+      if (mx.tail_rec[k] >= 0) {
+        const int64_t first = reinterpret_cast<const Span*>(m + at)->key_begin / ps;
+        for (int64_t j = std::max<int64_t>(0, from - first); j < std::min<int64_t>(32, np - first); ++j)
+          patch((size_t)mx.tail_rec[k] + offsetof(ItemRec, page) + 4 * (size_t)j);
+      }
+    }
   }
   if (pages_moved) {
     mx.page_indptr.assign(f.seg_page_indptr, f.seg_page_indptr + S + 1);

@@ -1,0 +1,53 @@
+"""GPU checks of the metadata uploads between decode steps: after any sequence
+of in-place updates (growing and shrinking, pages opened and dropped) each
+double buffer holds what a whole upload of the plan would."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import params_of, to_device
+from paper_2509_02121_amd import halo
+from workloads import build_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _shortened(csr, w, cut):
+    """The forest with `cut` tokens fewer per segment, pages dropped with them."""
+    out = {k: (v.copy() if v is not None else None) for k, v in csr.items()}
+    out["seg_len"] = (csr["seg_len"] - cut).astype(np.int32)
+    pages = [w.seg_pages[s][:(int(n) + 15) // 16] for s, n in enumerate(out["seg_len"])]
+    out["seg_page_indptr"] = np.concatenate([[0], np.cumsum([len(p) for p in pages])]).astype(np.int32)
+    out["seg_page_ids"] = np.concatenate(pages).astype(np.int32)
+    return out
+
+
+@pytest.mark.parametrize("where", ["current stream", "copy stream", "own stream"])
+@pytest.mark.parametrize("dtype,n_req,private", [(torch.bfloat16, 9, 300), (torch.bfloat16, 3, 1500),
+                                                 (torch.float32, 5, 120)])
+def test_updates_reach_both_buffers(gpu_lib, where, dtype, n_req, private):
+    print(f"case: update uploads {where} {dtype} {n_req} x {private}", flush=True)
+    rng = np.random.default_rng(n_req)
+    seg_len = [200] + [int(x) for x in rng.integers(private, private * 5 // 4, size=n_req)]
+    w = to_device(build_workload("updates", 91, 8, 2, 64, dtype, seg_len, [[0, 1 + r] for r in range(n_req)],
+                                 value_scale=0.5))
+    full = w.forest_csr()
+    pa = halo.PrefixAttention(params_of(w), _shortened(full, w, np.array([0] + [60] * n_req)), "cuda")
+    pa.IN_ORDER_KV_BYTES = 0 if where == "copy stream" else pa.IN_ORDER_KV_BYTES
+    stream = torch.cuda.Stream() if where == "own stream" else None
+    whole = torch.empty_like(pa.meta)
+    applied = 0
+    for low, high in ((40, 60), (20, 41), (0, 3), (0, 1), (30, 31), (10, 55), (0, 20), (0, 1)):
+        cut = np.array([0] + [int(x) for x in rng.integers(low, high, size=n_req)])
+        applied += pa.update(_shortened(full, w, cut), stream)
+        o, lse = pa.run(w.q, w.k_pool, w.v_pool)
+        if whole.numel() < pa.plan.device_meta_bytes:
+            whole = torch.empty_like(pa.meta)
+        pa.plan.upload(whole)
+        o2, lse2 = pa.alloc_outputs(w.q)
+        halo.prefix_attn_decode(pa.plan, whole, w.q, w.k_pool, w.v_pool, o2, lse2, pa.workspace)
+        torch.cuda.synchronize()
+        assert torch.equal(o, o2) and torch.equal(lse, lse2), f"cut {cut}"
+        assert not torch.isnan(o).any()
+    assert applied >= 6, "updates are mostly in place"
