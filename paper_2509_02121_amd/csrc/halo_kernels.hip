@@ -72,18 +72,8 @@ __device__ __forceinline__ u32x4_t ld16(const void* p) {
   if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   else return *reinterpret_cast<const u32x4_t*>(p);
 }
-template <bool NT>
-__device__ __forceinline__ u32x2_t ld8(const void* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(p));
-  else return *reinterpret_cast<const u32x2_t*>(p);
-}
-
 // K fragment: dims d0..d0+7 of key t in a K tile stored as [D/E][16][E]
 // (E elements per 16-byte unit).
-template <bool NT>
-__device__ __forceinline__ bf16x8_t load_k8(const __bf16* tile, int t, int d0) {
-  return __builtin_bit_cast(bf16x8_t, ld16<NT>(tile + ((d0 >> 3) * 16 + t) * 8));
-}
 template <bool NT>
 __device__ __forceinline__ f32x8_t load_k8(const float* tile, int t, int d0) {
   const u32x4_t lo = ld16<NT>(tile + ((d0 >> 2) * 16 + t) * 4);
@@ -94,10 +84,6 @@ __device__ __forceinline__ f32x8_t load_k8(const float* tile, int t, int d0) {
 // V fragment: the 8 slot-ordered keys at element offset off of a V tile
 // stored dim-major as [D][16] (one dim row holds tokens 0-3, 8-11, 4-7,
 // 12-15, so slots 8h..8h+7 are the keys one lane multiplies).
-template <bool NT>
-__device__ __forceinline__ bf16x8_t load_v8(const __bf16* page, int off) {
-  return __builtin_bit_cast(bf16x8_t, ld16<NT>(page + off));
-}
 template <bool NT>
 __device__ __forceinline__ f32x8_t load_v8(const float* page, int off) {
   const u32x4_t lo = ld16<NT>(page + off);
@@ -372,32 +358,50 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, const Item& it, cons
     p.pid1 = p.has1 ? __builtin_amdgcn_readlane(st.vpid, j + 1) : p.pid0;
     return p;
   };
-  // bf16: a position past the item's end loads, in every lane, the same one
-  // of 16 distinct 16-byte words at the start of the item table (at least
-  // 8 workgroups x 8 slots x 64 bytes; cached after its first use) instead
-  // of K/V pages: the count of loads in flight stays fixed (the loop's
-  // waits are static) without reading pages again and waiting for them
-  // when the item ends (measured: 70B-shaped decode 918.6 -> 912 us,
-  // two-level tree -1.6%, Llama-8B-shaped -2.5%).
-  const uint8_t* idle_words = reinterpret_cast<const uint8_t*>(a.items);
+  // bf16: a step's addresses are, per lane, a scalar base chosen by page and
+  // an offset that never changes; its loads differ only in their immediate
+  // offsets (K: +1 KB per 32 dims, +128 for keys 8-15; V: +512 per 16 dims).
+  // With an address worked out for every load: Llama-8B-shaped decode 22.1 ->
+  // 21.7 us, 4 requests of 12000-24000 keys 54.2 -> 53.2, two-level tree at d
+  // 64 64.6 -> 64.1. (fp32, bound by its products, lost 3% to it.)
+  // A position past the item's end loads, in every lane, the same one of 16
+  // distinct 16-byte words at the start of the item table (at least 8
+  // workgroups x 8 slots x 64 bytes; cached after its first use) instead of
+  // K/V pages: the count of loads in flight stays fixed (the loop's waits
+  // are static) without reading pages again and waiting for them when the
+  // item ends (measured: 70B-shaped decode 918.6 -> 912 us, two-level tree
+  // -1.6%, Llama-8B-shaped -2.5%).
+  auto uniform64 = [](int64_t x) {   // on the scalar unit
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+  };
+  const uint32_t k_lane = (grp * 16 + (col & 7)) * 16;   // unit grp, key col % 8
+  const uint32_t v_lane = v_off * (int)sizeof(T);
   auto fetch = [&](const StepPos& p, Regs& r) {
     // A rows 0-7 come from page 0, rows 8-15 from page 1; a V lane reads
     // page grp / 2.
-    const T* kq = kbase + (int64_t)(col < 8 ? p.pid0 : p.pid1) * page_stride;
-    const T* vq = vbase + (int64_t)(grp < 2 ? p.pid0 : p.pid1) * page_stride;
     if constexpr (sizeof(T) == 2) {
       const bool live = p.valid;
-      auto word = [&](const T* real, int k) {
-        return live ? reinterpret_cast<const uint8_t*>(real) : idle_words + 16 * k;
-      };
+      const int64_t idle = reinterpret_cast<int64_t>(a.items);
+      const int64_t o0 = (int64_t)(uint32_t)p.pid0 * page_stride * (int64_t)sizeof(T);
+      const int64_t o1 = (int64_t)(uint32_t)p.pid1 * page_stride * (int64_t)sizeof(T);
+      const int64_t k0 = uniform64(live ? reinterpret_cast<int64_t>(kbase) + o0 : idle);
+      const int64_t k1 = uniform64(live ? reinterpret_cast<int64_t>(kbase) + o1 : idle);
+      const int64_t v0 = uniform64(live ? reinterpret_cast<int64_t>(vbase) + o0 : idle);
+      const int64_t v1 = uniform64(live ? reinterpret_cast<int64_t>(vbase) + o1 : idle);
+      const uint8_t* kq = reinterpret_cast<const uint8_t*>((col < 8 ? k0 : k1) + (live ? k_lane : 0u));
+      const uint8_t* vq = reinterpret_cast<const uint8_t*>((grp < 2 ? v0 : v1) + (live ? v_lane : 0u));
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        r.k[0][s] = __builtin_bit_cast(F, ld16<NT>(word(kq + ((4 * s + grp) * 16 + (col & 7)) * 8, 2 * s)));
-        r.k[1][s] = __builtin_bit_cast(F, ld16<NT>(word(kq + ((4 * s + grp) * 16 + 8 + (col & 7)) * 8, 2 * s + 1)));
+        r.k[0][s] = __builtin_bit_cast(F, ld16<NT>(kq + s * 1024));
+        r.k[1][s] = __builtin_bit_cast(F, ld16<NT>(kq + s * 1024 + 128));
       }
 #pragma unroll
-      for (int b = 0; b < NB; ++b) r.v[b] = __builtin_bit_cast(F, ld16<NT>(word(vq + v_off + b * 256, 2 * NS + b)));
+      for (int b = 0; b < NB; ++b) r.v[b] = __builtin_bit_cast(F, ld16<NT>(vq + b * 512));
     } else {
+      const T* kq = kbase + (int64_t)(col < 8 ? p.pid0 : p.pid1) * page_stride;
+      const T* vq = vbase + (int64_t)(grp < 2 ? p.pid0 : p.pid1) * page_stride;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         r.k[0][s] = load_k8<NT>(kq, col & 7, 32 * s + 8 * grp);
@@ -466,9 +470,28 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, const Item& it, cons
 #pragma unroll
     for (int j = 1; j < 8; ++j) mt = fmaxf(mt, sv[j]);
     mt = rows_max(mt);
-    const float m_new = fmaxf(m, mt);
-    const float m_use = m_new == kNegInf ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+    // bf16 at d = 128: the sums are rescaled only when some row's maximum
+    // moves. (fp32 does it in the shadow of its products, which a branch would
+    // cut apart; at d = 64 the branch costs as much as the 16 products: 64
+    // requests on 2048 keys 13.6 -> 14.2 us.)
+    constexpr bool kLazy = sizeof(T) == 2 && D == 128;
+    float m_use, alpha = 1.f;
+    if constexpr (kLazy) {
+      if (__any(mt > m)) {
+        const float m_new = fmaxf(m, mt);
+        const float x = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+        lsum *= x;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] *= x;
+        m = m_new;
+      }
+      m_use = m == kNegInf ? 0.f : m;
+    } else {
+      const float m_new = fmaxf(m, mt);
+      m_use = m_new == kNegInf ? 0.f : m_new;
+      alpha = __builtin_amdgcn_exp2f(m - m_use);
+      m = m_new;
+    }
     float pr[8];
     float psum = 0.f;
 #pragma unroll
@@ -476,11 +499,12 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, const Item& it, cons
       pr[j] = __builtin_amdgcn_exp2f(sv[j] - m_use);
       psum += pr[j];
     }
-    lsum = lsum * alpha + psum;
-    m = m_new;
+    lsum = kLazy ? lsum + psum : lsum * alpha + psum;
     const F pf = to_frag(pr, (F*)nullptr);
+    if constexpr (!kLazy) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] *= alpha;
+      for (int b = 0; b < NB; ++b) acc[b] *= alpha;
+    }
     if (p.t0 + kKeysPerStep <= p.key_end) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[b] = mma(r.v[b], pf, acc[b]);
