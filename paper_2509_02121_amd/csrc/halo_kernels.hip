@@ -1638,13 +1638,17 @@ extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* 
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta must be 256-byte aligned");
   // The words an in-place update writes go as patches; where they would be
   // more bytes than the sections they lie in (between the segment length table
-  // and the row table, in that order in the image), the sections go whole.
+  // and the row table, in that order in the image), the sections go whole. So
+  // they do into a graph under capture: its replays read the image as it is
+  // then, where a list of patches would be the captured update's.
   const std::vector<Patch>& patches = plan->append.patches;
   const size_t at = plan->layout.seg_len, end = plan->layout.rows;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* meta = static_cast<uint8_t*>(device_meta);
   const size_t bytes = patches.size() * sizeof(Patch);
-  if (patches.size() > plan->layout.max_patches || bytes >= end - at)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  if (patches.size() > plan->layout.max_patches || bytes >= end - at || capture != hipStreamCaptureStatusNone)
     return upload_bytes(meta + at, plan->meta.data() + at, end - at, st);
   if (patches.empty()) return HALO_OK;
   const halo_status_t rc = upload_bytes(meta + plan->layout.patches, patches.data(), bytes, st);

@@ -51,3 +51,32 @@ def test_updates_reach_both_buffers(gpu_lib, where, dtype, n_req, private):
         assert torch.equal(o, o2) and torch.equal(lse, lse2), f"cut {cut}"
         assert not torch.isnan(o).any()
     assert applied >= 6, "updates are mostly in place"
+
+
+def test_captured_upload_follows_the_plan(gpu_lib):
+    """A captured update upload copies, on each replay, the image as the plan
+    has it by then."""
+    print("case: captured update upload", flush=True)
+    seg_len = [200, 330, 310, 350]
+    w = to_device(build_workload("updates", 92, 8, 2, 64, torch.bfloat16, seg_len, [[0, 1], [0, 2], [0, 3]],
+                                 value_scale=0.5))
+    full = w.forest_csr()
+    pa = halo.PrefixAttention(params_of(w), _shortened(full, w, np.array([0, 60, 60, 60])), "cuda")
+    plan, meta = pa.plan, pa.meta
+    assert plan.update_lengths(_shortened(full, w, np.array([0, 50, 52, 50])))
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        plan.upload_update(meta, side)
+    whole = torch.empty_like(meta)
+    for cut in (50, 31, 12, 33, 0):
+        assert plan.update_lengths(_shortened(full, w, np.array([0, cut, cut // 2, cut])))
+        g.replay()
+        plan.upload(whole)
+        torch.cuda.synchronize()
+        (o, lse), (o2, lse2) = pa.alloc_outputs(w.q), pa.alloc_outputs(w.q)
+        halo.prefix_attn_decode(plan, meta, w.q, w.k_pool, w.v_pool, o, lse, pa.workspace)
+        halo.prefix_attn_decode(plan, whole, w.q, w.k_pool, w.v_pool, o2, lse2, pa.workspace)
+        torch.cuda.synchronize()
+        assert torch.equal(o, o2) and torch.equal(lse, lse2), f"cut {cut}"
