@@ -200,10 +200,15 @@ struct ItemSize {
 // 1.25). The merge launch takes 4, and the partial results, fp32, written and
 // read, move at 8 TB/s. Measured, uncut and cut: one request of 901 tokens on
 // 4999 cached ones 121 -> 102, of 64 on 5000 105 -> 23, of 8 on 5000 89 -> 15;
-// fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181 -> 132.
+// fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181 -> 136.
 PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int head_dim, bool wide) {
   constexpr int32_t kMinItem = 16, kMinPiece = 4;        // steps: below, a piece is mostly its start and end
   constexpr int64_t kMaxBytes = (int64_t)256 << 20;      // of partial results
+  // Planning a piece takes the host about 0.4 us, once for all the layers that
+  // use the plan (tens of calls): of cuts that are about as fast the one of
+  // fewer pieces (4 fp32 requests of 64-256 on 1000: 3300 pieces in place of
+  // 4400, one of 2 requests 1050 in place of 1980).
+  constexpr double kHostPiece = 0.005;
   const int64_t per_cu = wide ? 2 : 4;                   // items a CU holds at once
   int64_t total = 0;
   int32_t longest = 0;
@@ -220,50 +225,59 @@ PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int h
   std::vector<int32_t> ends;
   std::vector<std::pair<double, int32_t>> parts;   // (CU time, steps)
   std::vector<double> cus;
-  auto estimate = [&](const PieceCut& cut) {
+  const int n_cus = std::max(1, kNumCUs / n_kv_heads);
+  const size_t group = wide ? 1 : 4;   // a workgroup's items end together: wide ones are alone in theirs
+  // The estimate of one cut, or infinity where its longest chain or its work
+  // spread evenly already shows that it is not below `least` (which spares
+  // many cuts the sort and the dealing).
+  auto estimate = [&](const PieceCut& cut, double least) {
     parts.clear();
     int64_t part_rows = 0;
-    double last = 0;
+    double last = 0, sum = 0;
     for (const ItemSize& x : items) {
       cut.ends(x.steps, ends);
       for (size_t k = 0; k < ends.size(); ++k) {
         const int32_t n = ends[k] - (k ? ends[k - 1] : 0);
         parts.emplace_back(wide ? 2.0 + n * row_step * (1 + (x.rows + 31) / 32) : 3.5 + n * row_step, n);
         last = std::max(last, (wide ? 5.0 : 3.5) + n * chain_step);
+        sum += parts.back().first;
       }
       if (ends.size() > 1) part_rows += (int64_t)ends.size() * x.rows;
     }
     part_rows *= n_kv_heads;
     const int64_t bytes = part_rows * (head_dim + 1) * 4;
-    if (bytes > kMaxBytes) return std::numeric_limits<double>::infinity();
+    const double rest = (part_rows ? 4.0 + 2.0 * bytes / 8e6 : 0.0) + kHostPiece * parts.size() * n_kv_heads;
+    if (bytes > kMaxBytes || std::max(last, 0.999 * sum / (group * n_cus)) + rest >= least)
+      return std::numeric_limits<double>::infinity();
     std::sort(parts.begin(), parts.end(), std::greater<std::pair<double, int32_t>>());
-    // a workgroup's items end together: wide ones are alone in theirs
-    const size_t group = wide ? 1 : 4;
-    cus.assign(std::max(1, kNumCUs / n_kv_heads), 0.0);   // min-heap of the CUs' end times
+    cus.assign(n_cus, 0.0);   // min-heap of the CUs' end times
     for (size_t i = 0; i < parts.size(); i += group) {
       std::pop_heap(cus.begin(), cus.end(), std::greater<double>());
       cus.back() += parts[i].first;
       last = std::max(last, cus.back());
       std::push_heap(cus.begin(), cus.end(), std::greater<double>());
     }
-    return last + (part_rows ? 4.0 + 2.0 * bytes / 8e6 : 0.0);
+    return last + rest;
   };
   PieceCut best;
-  double least = 0.95 * estimate(best);   // a cut has to bring something
-  for (int rounds = 1; rounds <= 4; ++rounds)
-    for (int64_t at_once : {kNumCUs * per_cu / 2, kNumCUs * per_cu}) {
-      PieceCut cut;
-      cut.length = (int32_t)std::max<int64_t>(kMinPiece, (total + at_once * rounds - 1) / (at_once * rounds));
-      if (cut.length >= longest) continue;
-      for (bool equal : {true, false}) {
-        cut.equal = equal;
-        const double t = estimate(cut);
-        if (t < least) {
-          least = t;
-          best = cut;
-        }
+  double least = 0.95 * estimate(best, std::numeric_limits<double>::infinity());   // a cut has to bring something
+  // 1 to 4, 6 and 8 half rounds of items on the chip
+  int32_t tried = longest;
+  for (int halves : {1, 2, 3, 4, 6, 8}) {
+    const int64_t n = (int64_t)kNumCUs * per_cu / 2 * halves;
+    PieceCut cut;
+    cut.length = (int32_t)std::max<int64_t>(kMinPiece, (total + n - 1) / n);
+    if (cut.length >= tried) continue;
+    tried = cut.length;
+    for (bool equal : {true, false}) {
+      cut.equal = equal;
+      const double t = estimate(cut, least);
+      if (t < least) {
+        least = t;
+        best = cut;
       }
     }
+  }
   return best;
 }
 
@@ -959,10 +973,11 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       }
     }
     std::stable_sort(units.begin(), units.end(), [](const Unit& a, const Unit& b) { return a.cost > b.cost; });
-    std::vector<std::vector<int32_t>> blk;
+    // the items of each workgroup: blk[b * cap ..], count[b] of them
+    std::vector<int32_t> blk, count;
     if (rounds) {
-      // per XCD, its workgroups in launch order; the last one is open
-      std::vector<std::vector<std::vector<int32_t>>> xb(8);
+      // per XCD, the same of its workgroups in launch order; the last one is open
+      std::vector<int32_t> xb[8], xcount[8];
       std::vector<int64_t> xitems(8, 0);
       for (const Unit& u : units) {
         int x = 0;
@@ -972,16 +987,25 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
           for (int y = 1; y < 8; ++y)
             if (xitems[y] < xitems[x]) x = y;
         }
-        if (xb[x].empty() || (int)xb[x].back().size() + u.count > cap) xb[x].emplace_back();
-        for (int32_t k = 0; k < u.count; ++k) xb[x].back().push_back(u.first + k);
+        if (xcount[x].empty() || xcount[x].back() + u.count > cap) {
+          xcount[x].push_back(0);
+          xb[x].resize(xb[x].size() + cap);
+        }
+        int32_t* at = xb[x].data() + xb[x].size() - cap + xcount[x].back();
+        for (int32_t k = 0; k < u.count; ++k) at[k] = u.first + k;
+        xcount[x].back() += u.count;
         xitems[x] += u.count;
       }
       size_t per_xcd = 0;
-      for (int x = 0; x < 8; ++x) per_xcd = std::max(per_xcd, xb[x].size());
+      for (int x = 0; x < 8; ++x) per_xcd = std::max(per_xcd, xcount[x].size());
       nb = 8 * (int64_t)per_xcd;
-      blk.assign(nb, {});
+      blk.resize(nb * cap);
+      count.assign(nb, 0);
       for (int x = 0; x < 8; ++x)
-        for (size_t j = 0; j < xb[x].size(); ++j) blk[j * 8 + x].swap(xb[x][j]);
+        for (size_t j = 0; j < xcount[x].size(); ++j) {
+          std::copy_n(xb[x].begin() + j * cap, xcount[x][j], blk.begin() + (j * 8 + x) * cap);
+          count[j * 8 + x] = xcount[x][j];
+        }
     }
     if (nb * slots > (int64_t)std::numeric_limits<int32_t>::max()) {
       fail(HALO_ERR_INVALID_ARGUMENT, "too many narrow work items");
@@ -992,21 +1016,23 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     using Slot = std::pair<int64_t, int32_t>;
     std::vector<std::priority_queue<Slot, std::vector<Slot>, std::greater<Slot>>> heap(8);
     if (!rounds) {
-      blk.assign(nb, {});
+      blk.resize(nb * cap);
+      count.assign(nb, 0);
       for (int32_t b = 0; b < (int32_t)nb; ++b) heap[b % 8].push(Slot{0, b});
     }
-    // place `count` items from `first` on the least loaded block of XCD x
+    // place `n_place` items from `first` on the least loaded block of XCD x
     // with room for them; false if there is none
-    auto place_on = [&](int x, int32_t first, int32_t count, int64_t cost) {
+    auto place_on = [&](int x, int32_t first, int32_t n_place, int64_t cost) {
       std::vector<Slot> aside;
       bool ok = false;
       while (!heap[x].empty()) {
         Slot s0 = heap[x].top();
         heap[x].pop();
-        if ((int)blk[s0.second].size() + count <= cap) {
-          for (int32_t k = 0; k < count; ++k) blk[s0.second].push_back(first + k);
+        int32_t& have = count[s0.second];
+        if (have + n_place <= cap) {
+          for (int32_t k = 0; k < n_place; ++k) blk[(int64_t)s0.second * cap + have++] = first + k;
           s0.first += cost;
-          if ((int)blk[s0.second].size() < cap) heap[x].push(s0);
+          if (have < cap) heap[x].push(s0);
           ok = true;
           break;
         }
@@ -1040,9 +1066,9 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     dealt.assign((size_t)(nb * slots), Item{});
     recs.assign((size_t)(nb * slots), ItemRec{});
     for (int64_t b = 0; b < nb; ++b)
-      for (size_t k = 0; k < blk[b].size(); ++k) {
+      for (int32_t k = 0; k < count[b]; ++k) {
         const size_t at = (size_t)(b * slots) + k;
-        const Item& it = items[blk[b][k]];
+        const Item& it = items[blk[b * cap + k]];
         dealt[at] = it;
         ItemRec& rc = recs[at];
         for (int r = 0; r < 16; ++r) {
