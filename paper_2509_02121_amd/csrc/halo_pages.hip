@@ -62,44 +62,21 @@ __device__ __forceinline__ int last_at_or_below(const int32_t* indptr, int n, in
   return lo + 63 - __clzll(mask);
 }
 
-// The (page slot, head) tiles of all sequences, in order, are cut into equal
-// contiguous runs, one per wave, so a few long sequences among many short
-// ones spread over the whole grid. A wave finds the sequence of its first
-// tile by binary search over seq_page_indptr and walks forward from there.
-// Per tile it reads the tile in its stored order with 16-byte loads
-// (coalesced), stages it token-major in its own LDS buffer ([16][D + E]
-// words, rows 16-byte aligned) and writes the tile's tokens as dense rows,
-// 16 bytes per lane. K vectors hold E dims of one token and move whole; V
-// vectors hold one dim of E tokens and are split into single words on the
-// way into LDS. W is an unsigned word of the element's width, so every bit
-// pattern (NaN payloads included) moves unchanged. Bound by HBM: tiles are
-// read and rows written once, past the caches (64 sequences of 256-2048
-// tokens, K and V, 595 MB: 134 -> 124.4 us, 4.8 TB/s, a device copy's rate;
-// 60 MB 39 -> 34 us).
-template <typename W, int D>
-__global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
+// Tiles t_begin .. t_end - 1 by one wave; `stage`: its LDS buffer. The two
+// kinds of loads are two loops: in one, the compiler merges them and drops the
+// non-temporal hint.
+template <typename W, int D, bool STREAM>
+__device__ __forceinline__ void gather_run(const GatherArgs& a, u32x4_t* stage, int first, int64_t t_begin,
+                                           int64_t t_end, int lane) {
   constexpr int E = 16 / (int)sizeof(W);   // elements per 16-byte vector
   constexpr int VPT = D / E;               // vectors per token and head
   constexpr int NV = 16 * VPT / 64;        // vectors per lane for a tile
   constexpr int ROW = D + E;               // staged row, in words (16-byte aligned)
-  __shared__ u32x4_t stage[4][16 * ROW / E];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int H = a.num_kv_heads;
   const int64_t row = (int64_t)H * D;      // output elements per token
   const W* pool = static_cast<const W*>(a.pool);
   W* out = static_cast<W*>(a.out);
-  W* st = reinterpret_cast<W*>(stage[wave]);
-
-  // page-list slots first .. last-1 are tiled; first need not be 0 (a
-  // slice of a larger page list)
-  const int first = a.seq_page_indptr[0];
-  const int64_t total = ((int64_t)a.seq_page_indptr[a.num_seqs] - first) * H;
-  const int64_t waves = (int64_t)gridDim.x * 4;
-  const int64_t per = (total + waves - 1) / waves;
-  const int64_t w_id = (int64_t)blockIdx.x * 4 + wave;
-  const int64_t t_begin = w_id * per;
-  const int64_t t_end = min(total, t_begin + per);
-  if (t_begin >= t_end) return;
+  W* st = reinterpret_cast<W*>(stage);
   // indptr[0] <= first + t_begin / H, so the search returns a sequence in
   // [0, num_seqs); the walk below stops at num_seqs - 1 at the latest, since
   // every slot is < indptr[num_seqs]
@@ -122,8 +99,9 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     const int n = min(16, len - t0);
     const W* src = pool + ((int64_t)pid * H + h) * 16 * D;
     u32x4_t v[NV];
+    const u32x4_t* src16 = reinterpret_cast<const u32x4_t*>(src) + lane;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(src) + lane + 64 * i);
+    for (int i = 0; i < NV; ++i) v[i] = STREAM ? __builtin_nontemporal_load(src16 + 64 * i) : src16[64 * i];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int idx = lane + 64 * i;
@@ -150,6 +128,48 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+}
+
+// The (page slot, head) tiles of all sequences, in order, are cut into equal
+// contiguous runs, one per wave, so a few long sequences among many short
+// ones spread over the whole grid. A wave finds the sequence of its first
+// tile by binary search over seq_page_indptr and walks forward from there.
+// Per tile it reads the tile in its stored order with 16-byte loads
+// (coalesced), stages it token-major in its own LDS buffer ([16][D + E]
+// words, rows 16-byte aligned) and writes the tile's tokens as dense rows,
+// 16 bytes per lane. K vectors hold E dims of one token and move whole; V
+// vectors hold one dim of E tokens and are split into single words on the
+// way into LDS. W is an unsigned word of the element's width, so every bit
+// pattern (NaN payloads included) moves unchanged. Bound by HBM: tiles are
+// read and rows written once. Rows go past the caches, and so do the tiles of
+// a launch of more than kGatherCached bytes (64 sequences of 256-2048 tokens,
+// K and V, 595 MB: 134 -> 124.4 us, 4.8 TB/s, a device copy's rate). Tiles of
+// smaller launches may be in the last-level cache, which loads past the caches
+// would not use. K and V of 8 MB each, read again / after other work: all
+// cached 9.6 / 17.4 us, only rows past the caches 8.9 / 18.1, both 10.8 / 13.7;
+// of 128 MB each 113 / 137, 95 / 149 and 104 / 110.
+constexpr int64_t kGatherCached = (int64_t)64 << 20;
+template <typename W, int D>
+__global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
+  constexpr int E = 16 / (int)sizeof(W);
+  __shared__ u32x4_t stage[4][16 * (D + E) / E];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int H = a.num_kv_heads;
+
+  // page-list slots first .. last-1 are tiled; first need not be 0 (a
+  // slice of a larger page list)
+  const int first = a.seq_page_indptr[0];
+  const int64_t total = ((int64_t)a.seq_page_indptr[a.num_seqs] - first) * H;
+  const int64_t waves = (int64_t)gridDim.x * 4;
+  const int64_t per = (total + waves - 1) / waves;
+  const int64_t w_id = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t t_begin = w_id * per;
+  const int64_t t_end = min(total, t_begin + per);
+  if (t_begin >= t_end) return;
+  if (total * 16 * D * (int64_t)sizeof(W) > kGatherCached)
+    gather_run<W, D, true>(a, stage[wave], first, t_begin, t_end, lane);
+  else
+    gather_run<W, D, false>(a, stage[wave], first, t_begin, t_end, lane);
 }
 
 // ---------------------------------------------------------------- write path

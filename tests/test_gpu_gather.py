@@ -148,3 +148,18 @@ def test_gather_sliced_page_list(gpu_lib, kind):
     exp = _expected(w, sub, kind)
     assert np.array_equal(_bits(out[:total]), _bits(exp))
     assert (out[total:].float() == 7.0).all(), "gather wrote past the last token"
+
+
+@pytest.mark.parametrize("pages", [4096, 4097])
+@pytest.mark.parametrize("kind", [halo.HALO_POOL_K, halo.HALO_POOL_V])
+def test_gather_at_the_cached_size(gpu_lib, pages, kind):
+    """At 64 MB of tiles (4096 pages of 4 heads at d = 128) the loads of a
+    launch still go through the caches, one page more and they do not."""
+    print(f"case: gather {pages} pages kind {kind}", flush=True)
+    seg_len = [16 * (pages - 2000) - 5, 16 * 2000]
+    w = to_device(build_workload("cached", 4, 4, 4, 128, torch.bfloat16, seg_len, [[0], [1]], poison=False))
+    out = _gather(w, [0, 1], kind)
+    exp = _expected(w, [0, 1], kind)
+    n = exp.shape[0]
+    assert np.array_equal(_bits(out[:n]), _bits(exp))
+    assert (out[n:].float() == 7.0).all(), "gather wrote past the last token"
