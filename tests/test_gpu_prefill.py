@@ -93,3 +93,33 @@ def test_piecewise_prefill_on_two_streams_and_in_a_graph(gpu_lib):
         assert torch.equal(o, want) and torch.equal(lse, want_lse)
     for o, lse in outs:
         assert torch.equal(o, want) and torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("dtype,n_new", [(torch.bfloat16, 40), (torch.bfloat16, 3), (torch.float32, 40),
+                                         (torch.float32, 3)])
+@pytest.mark.parametrize("where", ["q", "k", "v"])
+def test_nan_inputs_stay_visible_through_the_pieces(gpu_lib, dtype, n_new, where):
+    """A NaN in a query, a cached key or a cached value reaches exactly the
+    outputs it belongs to, and LSE is -inf where the scores are NaN, in pieces
+    (merged by rows and by workgroups) as uncut."""
+    print(f"case: NaN in {where}, prefill {dtype} {n_new} tokens", flush=True)
+    w = to_device(build_workload("nan", 74, 4, 2, 128, dtype, [6000, n_new], [[0, 1]], [n_new], value_scale=0.5))
+    page = int(w.seg_pages[0][200])
+    hit = np.zeros((n_new, 4, 128), bool)
+    if where == "q":
+        w.q[n_new - 1, 0, 5] = float("nan")
+        hit[n_new - 1, 0] = True
+    elif where == "k":
+        w.k_pool[page, 0, 2, 7, 3] = float("nan")
+        hit[:, :2] = True
+    else:
+        w.v_pool[page, 0, 9, 4] = float("nan")
+        hit[:, :2, 9] = True
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    assert pa.plan.workspace_bytes > 0
+    o, lse = pa.run(w.q, w.k_pool, w.v_pool)
+    o2, lse2 = pa.alloc_outputs(w.q)
+    halo.prefix_attn_prefill(pa.plan, pa.meta, w.q, w.k_pool, w.v_pool, o2, lse2, None)
+    for got, got_lse in ((o, lse), (o2, lse2)):
+        assert (torch.isnan(got).cpu().numpy() == hit).all()
+        assert (torch.isneginf(got_lse).cpu().numpy() == (hit.all(axis=2) if where != "v" else False)).all()

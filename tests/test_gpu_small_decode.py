@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import assert_parity, oracle_for, run_library
+from gpu_helpers import assert_parity, oracle_for, run_library, to_device
 from paper_2509_02121_amd import halo
 from gpu_helpers import params_of
 from workloads import build_workload
@@ -63,3 +63,29 @@ def test_chunk_lengths_of_small_batches(gpu_lib, n_req, prefix, private, longest
     o, lse = pa.run(w.q, w.k_pool, w.v_pool)
     torch.cuda.synchronize()
     assert_parity(w, o.double().cpu().numpy(), lse.double().cpu().numpy(), ro, rl, rows, "grown")
+
+
+@pytest.mark.parametrize("keys", [200, 900, 9000])
+@pytest.mark.parametrize("where", ["q", "k", "v"])
+def test_nan_inputs_stay_visible_through_the_merge(gpu_lib, keys, where):
+    """A NaN in a query, a key or a value reaches exactly the outputs it
+    belongs to, however many partials (a few, more than 8, many) a row has."""
+    print(f"case: NaN in {where}, {keys} private keys", flush=True)
+    w = to_device(build_workload("nan", 83, 8, 2, 128, torch.bfloat16, [keys, keys - 7], [[0], [1]], value_scale=0.5))
+    page = int(w.seg_pages[0][3])
+    hit = np.zeros((2, 8, 128), bool)
+    if where == "q":
+        w.q[0, 0, 5] = float("nan")
+        hit[0, 0] = True
+    elif where == "k":
+        w.k_pool[page, 0, 2, 7, 3] = float("nan")
+        hit[0, :4] = True
+    else:
+        w.v_pool[page, 0, 9, 4] = float("nan")
+        hit[0, :4, 9] = True
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    assert pa.plan.stats()["num_partial_rows"] > 0
+    o, lse = pa.run(w.q, w.k_pool, w.v_pool)
+    assert (torch.isnan(o).cpu().numpy() == hit).all()
+    if where == "q":
+        assert float(lse[0, 0]) == -np.inf and torch.isfinite(lse[1]).all()
