@@ -87,5 +87,5 @@ def test_nan_inputs_stay_visible_through_the_merge(gpu_lib, keys, where):
     assert pa.plan.stats()["num_partial_rows"] > 0
     o, lse = pa.run(w.q, w.k_pool, w.v_pool)
     assert (torch.isnan(o).cpu().numpy() == hit).all()
-    if where == "q":
-        assert float(lse[0, 0]) == -np.inf and torch.isfinite(lse[1]).all()
+    # rows with NaN scores have LSE -inf, however they were split
+    assert (torch.isneginf(lse).cpu().numpy() == (hit.all(axis=2) if where != "v" else False)).all()
