@@ -8,6 +8,7 @@ the built library every call raises.
 
 import ctypes
 import os
+import threading
 
 import numpy as np
 
@@ -705,6 +706,7 @@ class PrefixAttention:
 
     IN_ORDER_KV_BYTES = 256 << 20
     IN_ORDER_META_BYTES = 1 << 20   # of a whole plan's metadata (a new plan)
+    MAX_WORKSPACES = 16
 
     def __init__(self, params, csr, device="cuda", options=None):
         import torch
@@ -714,11 +716,13 @@ class PrefixAttention:
         self.device = torch.device(device)
         self._metas = [self._meta_buffer(self.plan.device_meta_bytes), None]
         self._cur = 0
-        self.workspace = (torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
-                          if self.plan.workspace_bytes and not self.plan.is_prefill else None)
-        # a prefill's workspace, one per stream: its calls may overlap on
-        # several streams
-        self._prefill_ws = {}
+        # one workspace per stream (the MAX_WORKSPACES latest), so that calls
+        # may overlap on several streams; a call holds the lock while it
+        # enqueues its launches, so that several threads may use one stream
+        self._ws = {}
+        self._enqueue = threading.Lock()
+        if not self.plan.is_prefill:
+            self._workspace_on(None)
         self._copy_stream = torch.cuda.Stream(device=self.device)
         # runs that read buffer i since its last upload: an event after the
         # last run() per stream, and the streams of bound callables (whose
@@ -780,11 +784,6 @@ class PrefixAttention:
         nxt = 1 - self._cur
         if not applied:
             self.plan = Plan.from_csr(self.plan.params, csr, self.options)
-            ws_have = self.workspace.numel() if self.workspace is not None else 0
-            if not self.plan.is_prefill and self.plan.workspace_bytes > ws_have:
-                # runs in flight may still use the old workspace
-                torch.cuda.synchronize(self.device)
-                self.workspace = torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
         if self._metas[nxt] is None or self._metas[nxt].numel() < self.plan.device_meta_bytes:
             torch.cuda.synchronize(self.device)
             self._metas[nxt] = self._meta_buffer(self.plan.device_meta_bytes)
@@ -817,24 +816,42 @@ class PrefixAttention:
         ev.record(s)
         self._runs[self._cur][s] = ev
 
+    @property
+    def workspace(self):
+        """The workspace of this object's calls on the current stream (None if
+        the plan needs none)."""
+        return self._workspace_on(None)
+
     def _workspace_on(self, stream):
-        """The workspace of a call on `stream` (None: the current stream).
-        Decode: this object's own. Prefill: the stream's, or, while the
-        stream is being captured, a new one from the graph's own pool."""
+        """The workspace of a call on `stream` (None: the current stream): the
+        stream's own, or, while it is being captured, a new one from the
+        graph's pool."""
         import torch
-        if not self.plan.is_prefill:
-            return self.workspace
         if not self.plan.workspace_bytes:
             return None
-        s = stream if stream is not None else torch.cuda.current_stream(self.device)
-        ws = self._prefill_ws.get(s.cuda_stream)
-        with torch.cuda.stream(s):
-            if torch.cuda.is_current_stream_capturing():
-                return torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
-            if ws is None or ws.numel() < self.plan.workspace_bytes:
-                # (a smaller one goes back to this stream's memory, in order)
-                ws = torch.empty(self.plan.workspace_bytes, dtype=torch.uint8, device=self.device)
-                self._prefill_ws[s.cuda_stream] = ws
+        if stream is None:
+            return self._current_workspace(torch.cuda.current_stream(self.device))
+        with torch.cuda.stream(stream):
+            return self._current_workspace(stream)
+
+    def _current_workspace(self, s):
+        """_workspace_on(s) for the current stream s."""
+        import torch
+        n = self.plan.workspace_bytes
+        if not n:
+            return None
+        if torch.cuda.is_current_stream_capturing():
+            return torch.empty(n, dtype=torch.uint8, device=self.device)
+        key = s.cuda_stream
+        ws = self._ws.get(key)
+        if ws is None or ws.numel() < n:
+            ws = torch.empty(n, dtype=torch.uint8, device=self.device)
+            with self._enqueue:
+                # (what is dropped goes back to its stream's memory, in order)
+                self._ws.pop(key, None)
+                self._ws[key] = ws
+                if len(self._ws) > self.MAX_WORKSPACES:
+                    del self._ws[next(iter(self._ws))]
         return ws
 
     def alloc_outputs(self, q):
@@ -856,8 +873,9 @@ class PrefixAttention:
                 ws.data_ptr() if ws is not None else None,
                 ws.numel() if ws is not None else 0, _stream_handle(stream))
 
-        def call(_workspace=ws):   # (kept alive by the callable)
-            st = fn(*args)
+        def call(_workspace=ws, _enqueue=self._enqueue):   # (the workspace is kept alive by the callable)
+            with _enqueue:
+                st = fn(*args)
             if st != HALO_OK:
                 _check(st)
         return call
@@ -868,6 +886,8 @@ class PrefixAttention:
             lse = lse if lse is not None else lse_new
         fn = prefix_attn_prefill if self.plan.is_prefill else prefix_attn_decode
         s = self._before_run(stream)
-        fn(self.plan, self.meta, q, k_pool, v_pool, o, lse, self._workspace_on(s), s)
+        ws = self._current_workspace(s) if stream is None else self._workspace_on(s)
+        with self._enqueue:
+            fn(self.plan, self.meta, q, k_pool, v_pool, o, lse, ws, s)
         self._after_run(s)
         return o, lse

@@ -89,3 +89,58 @@ def test_nan_inputs_stay_visible_through_the_merge(gpu_lib, keys, where):
     assert (torch.isnan(o).cpu().numpy() == hit).all()
     # rows with NaN scores have LSE -inf, however they were split
     assert (torch.isneginf(lse).cpu().numpy() == (hit.all(axis=2) if where != "v" else False)).all()
+
+
+def test_decodes_on_two_streams_have_a_workspace_each(gpu_lib):
+    """Calls of one object on two streams, each with its own queries, write
+    their partials to different workspaces, and to a third while captured."""
+    print("case: small decode on two streams", flush=True)
+    w = to_device(build_workload("two streams", 84, 8, 2, 128, torch.bfloat16, [200, 250], [[0], [1]],
+                                 value_scale=0.5))
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    assert pa.plan.workspace_bytes > 0
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    qs = [w.q * x for x in (1.0, -2.0, 0.5)]
+    want = [pa.run(q, w.k_pool, w.v_pool) for q in qs]
+    torch.cuda.synchronize()
+    used = set()
+    lib_run = halo.prefix_attn_decode
+
+    def spy(plan, meta, q, k, v, o, lse, workspace, stream=None):
+        used.add(workspace.data_ptr())
+        lib_run(plan, meta, q, k, v, o, lse, workspace, stream)
+
+    halo.prefix_attn_decode = spy
+    try:
+        got = [pa.alloc_outputs(q) for q in qs]
+        torch.cuda.synchronize()
+        for _ in range(20):
+            for q, out, s in zip(qs, got, streams):
+                pa.run(q, w.k_pool, w.v_pool, *out, stream=s)
+        torch.cuda.synchronize()
+        assert len(used) == 2
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=streams[0]):
+            pa.run(qs[2], w.k_pool, w.v_pool, *got[2])
+        assert len(used) == 3
+    finally:
+        halo.prefix_attn_decode = lib_run
+    for _ in range(3):
+        for q, out, s in zip(qs, got, streams):
+            pa.run(q, w.k_pool, w.v_pool, *out, stream=s)
+        graph.replay()
+        torch.cuda.synchronize()
+        for (o, lse), (wo, wl) in zip(got, want):
+            assert torch.equal(o, wo) and torch.equal(lse, wl)
+
+
+def test_workspaces_of_many_streams_are_bounded(gpu_lib):
+    print("case: workspaces of many streams", flush=True)
+    w = to_device(build_workload("streams", 85, 8, 2, 128, torch.bfloat16, [200, 250], [[0], [1]], value_scale=0.5))
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    want, _ = pa.run(w.q, w.k_pool, w.v_pool)
+    torch.cuda.synchronize()
+    outs = [pa.run(w.q, w.k_pool, w.v_pool, stream=torch.cuda.Stream())[0] for _ in range(pa.MAX_WORKSPACES + 8)]
+    torch.cuda.synchronize()
+    assert len(pa._ws) <= pa.MAX_WORKSPACES
+    assert all(torch.equal(o, want) for o in outs)
