@@ -863,18 +863,40 @@ class PrefixAttention:
     def bind(self, q, k_pool, v_pool, o, lse, stream=None):
         """A zero-argument callable that enqueues run(q, k_pool, v_pool, o,
         lse) with every pointer converted once (for tight timing loops).
-        The tensors must stay alive while the callable is used."""
+        The tensors must stay alive while the callable is used. Its calls use
+        the workspace of the stream they are bound to, or, while that stream
+        is being captured, one from the graph's own pool: the graph may then
+        replay on any stream, beside any other call of this object."""
+        import torch
         fn = _LIB.halo_prefix_attn_prefill if self.plan.is_prefill else _LIB.halo_prefix_attn_decode
         ws = self._workspace_on(stream)
         _check_run(self.plan, self.meta, q, k_pool, v_pool, o, lse, ws)
-        self._bound[self._cur].add(self._before_run(stream))
-        args = (self.plan._handle, self.meta.data_ptr(), q.data_ptr(), k_pool.data_ptr(),
-                v_pool.data_ptr(), o.data_ptr(), lse.data_ptr() if lse is not None else None,
-                ws.data_ptr() if ws is not None else None,
-                ws.numel() if ws is not None else 0, _stream_handle(stream))
+        s = self._before_run(stream)
+        self._bound[self._cur].add(s)
+        tensors = (self.plan._handle, self.meta.data_ptr(), q.data_ptr(), k_pool.data_ptr(),
+                   v_pool.data_ptr(), o.data_ptr(), lse.data_ptr() if lse is not None else None)
+        handle = _stream_handle(s)
+        enqueue = self._enqueue
+        if ws is None:
+            args = (*tensors, None, 0, handle)
 
-        def call(_workspace=ws, _enqueue=self._enqueue):   # (the workspace is kept alive by the callable)
-            with _enqueue:
+            def call():
+                st = fn(*args)
+                if st != HALO_OK:
+                    _check(st)
+            return call
+
+        args = (*tensors, ws.data_ptr(), ws.numel(), handle)
+        capturing = torch.cuda.is_current_stream_capturing
+
+        def call(_workspace=ws):   # (kept alive by the callable)
+            if capturing():
+                with torch.cuda.stream(s):
+                    if capturing():
+                        own = torch.empty_like(_workspace)
+                        _check(fn(*tensors, own.data_ptr(), own.numel(), handle))
+                        return
+            with enqueue:
                 st = fn(*args)
             if st != HALO_OK:
                 _check(st)

@@ -61,38 +61,71 @@ def test_items_cut_into_pieces(gpu_lib, dtype, d, out_dtype, prefix, q_len):
     assert_parity(w, o2.double().cpu().numpy(), lse2.double().cpu().numpy(), ro, rl, rows, "uncut")
 
 
-def test_piecewise_prefill_on_two_streams_and_in_a_graph(gpu_lib):
-    """Calls of one object that overlap on two streams have a workspace each,
-    and a captured call replays with the eager call's bits."""
+class _Spy:
+    """The library, noting the workspace address of each prefill call."""
+
+    def __init__(self, lib):
+        self.lib, self.seen = lib, []
+
+    def __getattr__(self, name):
+        return getattr(self.lib, name)
+
+    def halo_prefix_attn_prefill(self, *args):
+        self.seen.append(args[7])
+        return self.lib.halo_prefix_attn_prefill(*args)
+
+
+def test_piecewise_prefill_on_two_streams_and_in_a_graph(gpu_lib, monkeypatch):
+    """Calls of one object, each with its own queries: those that overlap on
+    two streams have a workspace each, and so has every captured call, bound
+    before its capture to one stream and replayed on another beside eager
+    calls on the first."""
     print("case: prefill pieces on two streams, captured", flush=True)
     w = to_device(build_workload("streams", 73, 8, 2, 128, torch.bfloat16, [5000, 150], [[0, 1]], [150],
                                  value_scale=0.5))
+    spy = _Spy(halo._LIB)
+    monkeypatch.setattr(halo, "_LIB", spy)
     pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
     assert pa.plan.workspace_bytes > 0
-    want, want_lse = pa.run(w.q, w.k_pool, w.v_pool)
+    qs = [w.q * x for x in (1.0, -2.0, 0.5, 3.0, -1.0)]
+    want = [pa.run(q, w.k_pool, w.v_pool) for q in qs]
+    outs = [pa.alloc_outputs(q) for q in qs]
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
-    streams = [torch.cuda.Stream() for _ in range(2)]
-    outs = [pa.alloc_outputs(w.q) for _ in streams]
+    spy.seen.clear()
     for _ in range(20):
-        for s, (o, lse) in zip(streams, outs):
-            pa.run(w.q, w.k_pool, w.v_pool, o, lse, stream=s)
+        for i, s in ((0, side), (1, other)):
+            pa.run(qs[i], w.k_pool, w.v_pool, *outs[i], stream=s)
     torch.cuda.synchronize()
-    o, lse = pa.alloc_outputs(w.q)
-    side = torch.cuda.Stream()
-    call = pa.bind(w.q, w.k_pool, w.v_pool, o, lse, side)
-    call()
+    eager = set(spy.seen)
+    assert len(eager) == 2
+    # three callables of one stream, the first two captured
+    calls = [pa.bind(qs[i], w.k_pool, w.v_pool, *outs[i], side) for i in (2, 3, 4)]
+    calls[0]()
     torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=side):
-        call()
+    graphs = []
+    for call in calls[:2]:
+        spy.seen.clear()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=side):
+            call()
+        assert len(spy.seen) == 1 and spy.seen[0] not in eager
+        eager.add(spy.seen[0])
+    bound = calls[2]
+    del calls, call   # a graph needs nothing of its callable
     for _ in range(3):
-        o.zero_()
-        graph.replay()
-        pa.run(w.q, w.k_pool, w.v_pool)   # eager work between the replays
+        for o, lse in outs:
+            o.zero_()
         torch.cuda.synchronize()
-        assert torch.equal(o, want) and torch.equal(lse, want_lse)
-    for o, lse in outs:
-        assert torch.equal(o, want) and torch.equal(lse, want_lse)
+        with torch.cuda.stream(other):
+            graphs[0].replay()
+        graphs[1].replay()
+        bound()
+        for i, s in ((0, side), (1, other)):
+            pa.run(qs[i], w.k_pool, w.v_pool, *outs[i], stream=s)
+        torch.cuda.synchronize()
+        for (o, lse), (wo, wl) in zip(outs, want):
+            assert torch.equal(o, wo) and torch.equal(lse, wl)
 
 
 @pytest.mark.parametrize("dtype,n_new", [(torch.bfloat16, 40), (torch.bfloat16, 3), (torch.float32, 40),
