@@ -492,6 +492,25 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
             break;
           }
     }
+    // With a bf16 output, rows that one item holds at the longer chunks stay
+    // there: cut, they would be rounded to bf16 twice, as partial results and as
+    // merged ones (200-250 keys: relative error 1.84e-3 -> 2.41e-3; rows of
+    // several partials are anyway, and splitting them further leaves their error
+    // at 2.4e-3). It costs 16 requests of 250 keys 0.9 us of 8.2, 4 on 500 shared
+    // keys alone 4.9 of 7.
+    std::vector<char> one_item_req(R, 0), one_item_seg(S, 0);
+    if (p.out_dtype == HALO_BF16 && (kc_shared < 512 || kc_private < kc_private_default))
+      for (int r = 0; r < R; ++r) {
+        int64_t shared_chunks = 0, priv = 0;
+        for (int32_t i = path_begin(r); i < path_end(r); ++i) {
+          const int64_t n = paged(f.seg_len[f.req_seg_ids[i]]);
+          if (refs[f.req_seg_ids[i]] == 1) priv += n;
+          else shared_chunks += ceil_div(n, 512);
+        }
+        one_item_req[r] = shared_chunks == 0 ? priv <= kc_private_default : shared_chunks == 1 && priv == 0;
+        if (one_item_req[r])
+          for (int32_t i = path_begin(r); i < path_end(r); ++i) one_item_seg[f.req_seg_ids[i]] = 1;
+      }
     if (opt.kc_shared > 0) kc_shared = opt.kc_shared;
     if (opt.kc_private > 0) kc_private = opt.kc_private;
     int rows_per = kRowsPerItem;
@@ -521,7 +540,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     for (int s = 0; s < S; ++s) {
       if (refs[s] < 2 || f.seg_len[s] == 0) continue;
       std::vector<Span> sp;
-      pieces(s, f.seg_len[s], kc, sp);
+      pieces(s, f.seg_len[s], one_item_seg[s] && opt.kc_shared == 0 ? 512 : kc, sp);
       for (int g = 0; g < Hkv; ++g) {
         std::vector<Row> rows;
         for (int32_t r : seg_reqs[s])
@@ -547,16 +566,17 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     // Suffix pass: each request's private keys, in chunks.
     for (int r = 0; r < R; ++r) {
       std::vector<Span> sp;
+      const int32_t kc_own = one_item_req[r] && opt.kc_private == 0 ? kc_private_default : kc_private;
       for (int32_t i = path_begin(r); i < path_end(r); ++i) {
         const int32_t s = f.req_seg_ids[i];
-        if (refs[s] == 1 && f.seg_len[s] > 0) pieces(s, f.seg_len[s], kc_private, sp);
+        if (refs[s] == 1 && f.seg_len[s] > 0) pieces(s, f.seg_len[s], kc_own, sp);
       }
-      // pack consecutive pieces into chunks of at most kc_private keys
+      // pack consecutive pieces into chunks of at most kc_own keys
       std::vector<std::vector<Span>> chunks;
       int64_t cur = 0;
       for (const Span& piece : sp) {
         const int64_t n = paged(piece.key_end - piece.key_begin);
-        if (chunks.empty() || cur + n > kc_private) {
+        if (chunks.empty() || cur + n > kc_own) {
           chunks.emplace_back();
           cur = 0;
         }

@@ -65,7 +65,7 @@ def test_chunk_lengths_of_small_batches(gpu_lib, n_req, prefix, private, longest
     assert_parity(w, o.double().cpu().numpy(), lse.double().cpu().numpy(), ro, rl, rows, "grown")
 
 
-@pytest.mark.parametrize("keys", [200, 900, 9000])
+@pytest.mark.parametrize("keys", [300, 900, 9000])
 @pytest.mark.parametrize("where", ["q", "k", "v"])
 def test_nan_inputs_stay_visible_through_the_merge(gpu_lib, keys, where):
     """A NaN in a query, a key or a value reaches exactly the outputs it
@@ -95,7 +95,7 @@ def test_decodes_on_two_streams_have_a_workspace_each(gpu_lib):
     """Calls of one object on two streams, each with its own queries, write
     their partials to different workspaces, and to a third while captured."""
     print("case: small decode on two streams", flush=True)
-    w = to_device(build_workload("two streams", 84, 8, 2, 128, torch.bfloat16, [200, 250], [[0], [1]],
+    w = to_device(build_workload("two streams", 84, 8, 2, 128, torch.bfloat16, [300, 350], [[0], [1]],
                                  value_scale=0.5))
     pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
     assert pa.plan.workspace_bytes > 0
@@ -136,7 +136,7 @@ def test_decodes_on_two_streams_have_a_workspace_each(gpu_lib):
 
 def test_workspaces_of_many_streams_are_bounded(gpu_lib):
     print("case: workspaces of many streams", flush=True)
-    w = to_device(build_workload("streams", 85, 8, 2, 128, torch.bfloat16, [200, 250], [[0], [1]], value_scale=0.5))
+    w = to_device(build_workload("streams", 85, 8, 2, 128, torch.bfloat16, [300, 350], [[0], [1]], value_scale=0.5))
     pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
     want, _ = pa.run(w.q, w.k_pool, w.v_pool)
     torch.cuda.synchronize()
