@@ -173,9 +173,10 @@ halo_status_t halo_plan_create_with_options(const halo_attn_params_t* params,
  * unchanged (length and pages), and each changed segment's page list its
  * old list with pages appended at the end (or dropped from it). A private
  * segment of length n at planning time can take any length in
- * (b, n + append_reserve], b < n being the first key of its last span
- * (for the caller: any length >= its planning-time length up to the
- * reserve); its page table and last span were laid out with that room.
+ * (b, n + append_reserve], b < n being the first key of its last span or,
+ * where the planner chose key chunks of less than 256, of its last run of
+ * 256 keys (for the caller: any length >= its planning-time length up to
+ * the reserve); its page table and last span were laid out with that room.
  * Only span ends, the matching inline first-span copies and record page
  * ids, the new page ids, the segment length table and the statistics
  * change; the work decomposition stays the planning-time one. While no

@@ -174,10 +174,11 @@ struct DefaultInitAlloc : std::allocator<T> {
 // A decode plan's copy of its forest; per segment its page slots in the
 // image (page_slot_off, S + 1 entries: a private segment has room for the
 // pages its growth reserve needs) and the lengths it may take in place,
-// (len_lo, len_hi]; and per segment the spans that end at its last key (CSR
-// over segments: tail_span[tail_indptr[s] .. tail_indptr[s+1])), each with
-// the image byte offsets of the item whose first span it is and of that
-// item's lane record (-1 if none).
+// (len_lo, len_hi]; and per segment the spans whose end can change (CSR over
+// segments: tail_span[tail_indptr[s] .. tail_indptr[s+1])), those that end at
+// its last key and those past len_lo, each with the key its end never passes
+// (tail_end), and the image byte offsets of the item whose first span it is and
+// of that item's lane record (-1 if none).
 // patches: every image word an update has written since the plan was made,
 // as it is now (rebuilt by each update; more than MetaLayout::max_patches:
 // incomplete, the sections are uploaded instead). touched: the
@@ -189,7 +190,7 @@ struct Patch {
 struct AppendIndex {
   std::vector<int32_t> seg_len, page_indptr, page_ids, req_indptr, req_ids, refs;
   std::vector<int32_t> page_slot_off, len_lo, len_hi;
-  std::vector<int32_t> tail_indptr, tail_span;
+  std::vector<int32_t> tail_indptr, tail_span, tail_end;
   std::vector<int64_t> tail_item, tail_rec;
   std::vector<Patch> patches;
   std::vector<int32_t> touched, min_pages;   // min_pages: -1 until touched

@@ -409,6 +409,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   std::vector<MergeItem> merge_items;     // prefill: the items cut into pieces, and each piece's part_base
   std::vector<int32_t> merge_bases;
   int32_t n_chunks = 0;
+  bool short_private = false;   // decode: the planner's private chunks are below 256 keys
 
   if (!prefill) {
     // Private chunks: the longest of 2048, 1024, 512 and 256 keys that
@@ -513,6 +514,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       }
     if (opt.kc_shared > 0) kc_shared = opt.kc_shared;
     if (opt.kc_private > 0) kc_private = opt.kc_private;
+    short_private = opt.kc_private == 0 && kc_private < kc_private_default;
     int rows_per = kRowsPerItem;
     int kc = kc_shared;
     if (wide) {
@@ -1162,19 +1164,32 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   L.whole_items = place(sizeof(Item) * whole_items.size());
   L.whole_recs = place(sizeof(ItemRec) * whole_recs.size());
   L.whole_wide = place(sizeof(Item) * whole_witems.size());
+  // A decode plan's private segment can be shortened in place to more than
+  // tail_lo keys: the first key of its last span, or, where the planner's chunks
+  // are shorter than 256 keys, what a last span of a 256-key chunk would leave
+  // (spans past the new end then have no keys).
+  auto& tail_lo = scratch<std::vector<int32_t>, 22>();
+  tail_lo.assign(S, -1);
+  auto is_tail = [&](const Span& sp) {
+    return refs[sp.seg] == 1 ? sp.key_end > tail_lo[sp.seg] : sp.key_end == f.seg_len[sp.seg];
+  };
   // Room for the patches of the segments that can change: a length, the pages
-  // of the last spans and of the growth reserve, and per last span its end, the
-  // inline copy of it and the record's page ids.
+  // of the spans that can and of the growth reserve, and per such span its end,
+  // the inline copy of it and the record's page ids.
   if (!prefill) {
-    std::vector<size_t> pages(S, 0);
     for (const Span& sp : spans)
       if (refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg])
-        pages[sp.seg] = (size_t)(slot_off[sp.seg + 1] - slot_off[sp.seg]) - sp.key_begin / p.page_size;
+        tail_lo[sp.seg] = short_private ? std::min(sp.key_begin, (sp.key_end - 1) / 256 * 256) : sp.key_begin;
+    auto slots_from = [&](int32_t s, int32_t key) {
+      return (size_t)(slot_off[s + 1] - slot_off[s]) - std::max(key, 0) / p.page_size;
+    };
     for (int s = 0; s < S; ++s)
-      if (refs[s] < 2) L.max_patches += 1 + (refs[s] ? pages[s] : (size_t)(slot_off[s + 1] - slot_off[s]));
+      if (refs[s] < 2) L.max_patches += 1 + (refs[s] && tail_lo[s] < 0 ? 0 : slots_from(s, tail_lo[s]));
     for (const Span& sp : spans)
-      if (refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg])
-        L.max_patches += 2 + std::min<size_t>(32, pages[sp.seg]);
+      if (refs[sp.seg] == 1 && is_tail(sp))
+        L.max_patches += 2 + std::min<size_t>(32, sp.key_end == f.seg_len[sp.seg]
+                                                      ? slots_from(sp.seg, sp.key_begin)
+                                                      : (size_t)ceil_div(sp.key_end - sp.key_begin, p.page_size));
     // (an update that needs more uploads the sections whole)
     L.max_patches = std::min(L.max_patches, (L.rows - L.seg_len) / 4 / sizeof(Patch));
   }
@@ -1219,11 +1234,11 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   }
 
   // What halo_plan_update_lengths needs: the forest the plan was built for,
-  // the page slots, and for every segment the spans that end at its last
-  // key (with the image offsets of the item whose first span it is, whose
-  // inline copy of the span must follow, and of that item's lane record),
-  // and the lengths it may take in place: above the first key of each of
-  // those spans, and within their caps and the segment's page slots.
+  // the page slots, and for every segment the spans that an update can change
+  // (with the image offsets of the item whose first span it is, whose inline
+  // copy of the span must follow, and of that item's lane record), and the
+  // lengths it may take in place: above tail_lo, and within the last spans'
+  // caps and the segment's page slots.
   if (!prefill) {
     AppendIndex& ax = plan->append;
     const int64_t n_refs = f.req_seg_indptr[R];
@@ -1244,35 +1259,39 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       if (witems[i].n_spans > 0) first_of[witems[i].span_begin] = (int64_t)(L.wide_items + i * sizeof(Item));
     ax.tail_indptr.assign(S + 1, 0);
     for (const Span& sp : spans)
-      if (sp.key_end == f.seg_len[sp.seg]) ax.tail_indptr[sp.seg + 1]++;
+      if (is_tail(sp)) ax.tail_indptr[sp.seg + 1]++;
     for (int s = 0; s < S; ++s) ax.tail_indptr[s + 1] += ax.tail_indptr[s];
     ax.tail_span.resize(ax.tail_indptr[S]);
     ax.tail_item.resize(ax.tail_indptr[S]);
     ax.tail_rec.resize(ax.tail_indptr[S]);
-    ax.len_lo.assign(S, -1);
+    ax.tail_end.resize(ax.tail_indptr[S]);
+    ax.len_lo.assign(tail_lo.begin(), tail_lo.end());
     ax.len_hi.resize(S);
     // (lengths past the int32 range are never reached: clamp)
     auto clamp32 = [](int64_t v) { return (int32_t)std::min<int64_t>(v, std::numeric_limits<int32_t>::max()); };
     for (int s = 0; s < S; ++s)
       ax.len_hi[s] = refs[s] == 0 ? clamp32((int64_t)(slot_off[s + 1] - slot_off[s]) * p.page_size) : f.seg_len[s];
     std::vector<int32_t> fill(ax.tail_indptr.begin(), ax.tail_indptr.end() - 1);
+    std::vector<char> capped(S, 0);
     for (size_t i = 0; i < spans.size(); ++i) {
       const Span& sp = spans[i];
-      if (sp.key_end != f.seg_len[sp.seg]) continue;
+      if (!is_tail(sp)) continue;
       const int32_t k = fill[sp.seg]++;
+      const bool last = sp.key_end == f.seg_len[sp.seg];
+      ax.tail_end[k] = last ? std::numeric_limits<int32_t>::max() : sp.key_end;
       ax.tail_span[k] = (int32_t)i;
       ax.tail_item[k] = first_of[i];
       ax.tail_rec[k] = rec_of[i];
-      if (refs[sp.seg] == 1) {
+      if (refs[sp.seg] == 1 && last) {
         const int32_t s = sp.seg;
         const int32_t cap = rec_of[i] >= 0 ? kNarrowSpanKeys : kMaxSpanKeys;
         const int32_t slots_end = clamp32((int64_t)(slot_off[s + 1] - slot_off[s]) * p.page_size);
-        const bool first_tail = k == ax.tail_indptr[s];
-        ax.len_lo[s] = std::max(ax.len_lo[s], sp.key_begin);
-        ax.len_hi[s] = std::min(first_tail ? slots_end : ax.len_hi[s], clamp32((int64_t)sp.key_begin + cap));
+        ax.len_hi[s] = std::min(capped[s] ? ax.len_hi[s] : slots_end, clamp32((int64_t)sp.key_begin + cap));
+        capped[s] = 1;
       }
     }
     ax.patches.reserve(L.max_patches + 1);   // one more says that they are too many
+    ax.touched.reserve(S);
     ax.min_pages.assign(S, -1);
   }
 
@@ -1410,12 +1429,12 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
              sizeof(int32_t) * (np - np_old));
     for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
       Span* sp = reinterpret_cast<Span*>(m + L.spans) + mx.tail_span[k];
-      sp->key_end = len;
-      if (mx.tail_item[k] >= 0) reinterpret_cast<Item*>(m + mx.tail_item[k])->s0_key_end = len;
+      sp->key_end = std::max(sp->key_begin, std::min(len, mx.tail_end[k]));
+      if (mx.tail_item[k] >= 0) reinterpret_cast<Item*>(m + mx.tail_item[k])->s0_key_end = sp->key_end;
       if (mx.tail_rec[k] >= 0 && np != np_old) {
         // the record holds the span's first 32 page ids
         ItemRec* rc = reinterpret_cast<ItemRec*>(m + mx.tail_rec[k]);
-        const int64_t n = std::min<int64_t>(32, ceil_div(len - sp->key_begin, ps));
+        const int64_t n = std::min<int64_t>(32, ceil_div(sp->key_end - sp->key_begin, ps));
         for (int64_t j = 0; j < n; ++j) rc->page[j] = slots[sp->page_off + j];
       }
     }
@@ -1440,8 +1459,9 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
       patch(at + offsetof(Span, key_end));
       if (mx.tail_item[k] >= 0) patch((size_t)mx.tail_item[k] + offsetof(Item, s0_key_end));
       if (mx.tail_rec[k] >= 0) {
-        const int64_t first = reinterpret_cast<const Span*>(m + at)->key_begin / ps;
-        for (int64_t j = std::max<int64_t>(0, from - first); j < std::min<int64_t>(32, np - first); ++j)
+        const Span* sp = reinterpret_cast<const Span*>(m + at);
+        const int64_t first = sp->key_begin / ps, n = ceil_div(sp->key_end - sp->key_begin, ps);
+        for (int64_t j = std::max<int64_t>(0, from - first); j < std::min<int64_t>(32, n); ++j)
           patch((size_t)mx.tail_rec[k] + offsetof(ItemRec, page) + 4 * (size_t)j);
       }
     }

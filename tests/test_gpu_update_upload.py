@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import params_of, to_device
+from gpu_helpers import assert_parity, oracle_for, params_of, to_device
 from paper_2509_02121_amd import halo
 from workloads import build_workload
 
@@ -80,3 +80,32 @@ def test_captured_upload_follows_the_plan(gpu_lib):
         halo.prefix_attn_decode(plan, whole, w.q, w.k_pool, w.v_pool, o2, lse2, pa.workspace)
         torch.cuda.synchronize()
         assert torch.equal(o, o2) and torch.equal(lse, lse2), f"cut {cut}"
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_removed_tokens_reach_both_buffers(gpu_lib, dtype):
+    """Tokens are removed past the starts of short key chunks (whose spans are
+    then empty) and appended again: each update applies
+    and its upload gives the bits of a whole upload and the oracle's values."""
+    print(f"case: removed tokens {dtype}", flush=True)
+    seg_len = [200, 250, 510, 300]
+    w = to_device(build_workload("removed", 93, 8, 2, 128, dtype, seg_len, [[0, 1], [0, 2], [0, 3]],
+                                 value_scale=0.5 if dtype == torch.bfloat16 else 1.0))
+    full = w.forest_csr()
+    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    whole = torch.empty_like(pa.meta)
+    cuts = [[1, 1, 1], [249, 253, 43], [60, 100, 3], [0, 0, 0], [200, 190, 20], [130, 64, 40], [0, 0, 0]]
+    for cut in cuts:
+        csr = _shortened(full, w, np.array([0] + cut))
+        assert pa.update(csr), cut
+        o, lse = pa.run(w.q, w.k_pool, w.v_pool)
+        pa.plan.upload(whole)
+        o2, lse2 = pa.alloc_outputs(w.q)
+        halo.prefix_attn_decode(pa.plan, whole, w.q, w.k_pool, w.v_pool, o2, lse2, pa.workspace)
+        torch.cuda.synchronize()
+        assert torch.equal(o, o2) and torch.equal(lse, lse2), f"cut {cut}"
+        saved = w.seg_len
+        w.seg_len = csr["seg_len"]
+        ro, rl, rows = oracle_for(w)
+        w.seg_len = saved
+        assert_parity(w, o.double().cpu().numpy(), lse.double().cpu().numpy(), ro, rl, rows, f"cut {cut}")

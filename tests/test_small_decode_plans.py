@@ -54,3 +54,59 @@ def test_only_those_rows_stay_whole():
     # it whole for all
     m = _plan([400, 40, 50], [[0], [0, 1], [0, 2]], torch.bfloat16, torch.bfloat16).inspect()
     assert max(int(sp[2] - sp[1]) for sp in m["spans"] if sp[0] == 0) == 400
+
+
+def _covers(plan, csr):
+    """Each request's items cover the keys of its path, each once."""
+    m = plan.inspect()
+    items = m["items"].reshape(-1, 16)
+    got = {}
+    for it, rec in zip(items, m["item_recs"].reshape(-1, 64)):
+        if it[1] == 0:
+            continue
+        for k in range(it[3]):
+            seg, kb, ke, _, off = (int(x) for x in m["spans"][it[2] + k][:5])
+            assert kb <= ke
+            if k == 0:
+                assert (int(it[8]), int(it[9])) == (kb, ke)
+                n = min(32, (ke - kb + 15) // 16)
+                assert np.array_equal(rec[32:32 + n], m["page_ids"][off:off + n])
+            for row in m["rows"][it[0]:it[0] + it[1], 0]:
+                got.setdefault((int(row), seg), set()).update(range(kb, ke))
+    paths = [csr["req_seg_ids"][a:b] for a, b in zip(csr["req_seg_indptr"][:-1], csr["req_seg_indptr"][1:])]
+    for r, path in enumerate(paths):
+        for s in path:
+            for h in range(8):
+                assert got.get((r * 8 + h, int(s)), set()) == set(range(int(csr["seg_len"][s])))
+    for s, n in enumerate(csr["seg_len"]):
+        ids = csr["seg_page_ids"][csr["seg_page_indptr"][s]:csr["seg_page_indptr"][s + 1]]
+        off = m["seg_page_off"][s]
+        assert np.array_equal(m["page_ids"][off:off + len(ids)], ids)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [250, 257, 440, 700])
+def test_lengths_that_short_chunks_accept(n, dtype):
+    """Removing tokens: a private segment of n keys takes every length above
+    its last run of 256 keys, as with chunks of 256 keys, and grows again, on
+    other pages too; one key less asks for a new plan."""
+    paths = [[0, 1], [0, 2]]
+
+    def forest(length, own):
+        csr = _csr([700, length, 40], paths)
+        csr["seg_page_ids"] = np.concatenate([np.arange(44), own, np.arange(500, 503)]).astype(np.int32)
+        return csr
+
+    own = np.arange(44, 44 + (n + 15) // 16)
+    plan = halo.Plan.from_csr(halo.make_params(8, 2, 128, dtype, 1 << 16, 0.1), forest(n, own))
+    low = (n - 1) // 256 * 256
+    rng = np.random.default_rng(n)
+    for step, length in enumerate([n - 1, low + 1, n, low + 33, n + 200, low + 2, low + 70, low + 16, n]):
+        if length <= low:
+            continue
+        pages = (length + 15) // 16
+        own = np.concatenate([own[:pages], 1000 + 100 * step + rng.permutation(100)[:max(0, pages - len(own))]])
+        assert plan.update_lengths(forest(length, own)), (length, n)
+        _covers(plan, forest(length, own))
+    if low:
+        assert not plan.update_lengths(forest(low, own[:low // 16]))
