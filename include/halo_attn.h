@@ -200,13 +200,18 @@ halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_forest_t* f
 halo_status_t halo_plan_upload(const halo_plan_t* plan, void* device_meta,
                                size_t device_meta_bytes, void* stream);
 
-/* halo_plan_upload of only what halo_plan_update_lengths can change (the
- * segment lengths, page ids, work items, their records and spans: about
- * half of a decode plan's metadata), for a decode loop that updates its
- * plan in place every step. device_meta must already hold an upload of
- * this same plan (halo_plan_upload, or this call, after any number of
- * updates since); after halo_plan_create, use halo_plan_upload. Same
- * arguments, errors and lifetime rules as halo_plan_upload. */
+/* halo_plan_upload of only what halo_plan_update_lengths has changed, for a
+ * decode loop that updates its plan in place every step. device_meta must
+ * already hold an upload of this same plan (halo_plan_upload, or this call,
+ * after any number of updates since); after halo_plan_create, use
+ * halo_plan_upload. The words written by updates since the plan was made go
+ * through pinned memory of the library's own (at most 2 MB, kept until the
+ * process ends), from which a small kernel writes them into device_meta.
+ * Where they are more than 256 KB or a quarter of the sections they lie in
+ * (the segment lengths, page ids, work items, their records and spans: about
+ * half of the metadata), and into a graph under capture, those sections are
+ * copied instead. Same arguments, errors and lifetime rules as
+ * halo_plan_upload. */
 halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* device_meta,
                                       size_t device_meta_bytes, void* stream);
 

@@ -144,9 +144,7 @@ struct MetaLayout {
   size_t whole_items = 0;    // as items, item_recs and wide_items
   size_t whole_recs = 0;
   size_t whole_wide = 0;
-  // Room on the device for an update's patches (zero in the image).
-  size_t patches = 0;        // Patch [max_patches]
-  size_t max_patches = 0;
+  size_t max_patches = 0;    // more changed words than this: upload the sections
   size_t total = 0;
 };
 

@@ -26,11 +26,14 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <string>
 #include <type_traits>
+#include <vector>
 
 #include "halo_internal.h"
 
@@ -1613,12 +1616,77 @@ halo_status_t run_attention(const halo_plan_t* plan, bool want_prefill, const vo
 }  // namespace
 
 namespace {
-// An in-place update's changed words, written into the metadata image. The
-// words of a 70B-shaped decode step are 140 KB of patches where the sections
-// they lie in are 4 MB.
+// An in-place update's changed words, written into the metadata image (patches:
+// pinned host memory). The words of a 70B-shaped decode step are 140 KB of
+// patches where the sections they lie in are 4 MB.
 __global__ __launch_bounds__(256) void patch_kernel(int32_t* image, const Patch* patches, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) image[patches[i].word] = patches[i].value;
+}
+
+// Pinned buffers that patches travel in: the kernel reads them from there, so
+// an upload neither waits for the work ahead of it on its stream (a copy from
+// pageable memory does, which left the GPU idle until the host came back) nor
+// keeps the plan's memory in use. At most kMaxStages of kStageBytes, kept until
+// the process ends; a buffer is reused when the kernel that read it has ended.
+constexpr size_t kStageBytes = 256 << 10;
+constexpr size_t kMaxStages = 8;
+struct Stage {
+  Patch* host = nullptr;
+  hipEvent_t read = nullptr;   // after the last kernel that read it
+  int device = 0;
+};
+std::mutex g_stage_mu;
+std::vector<Stage> g_stages;   // least recently used first
+
+// While another thread captures a stream, the calls below must not count as
+// part of it.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// A buffer no kernel reads any more, moved to the end of g_stages; nullptr if
+// there is none and none can be had. g_stage_mu is held.
+Stage* free_stage(int device) {
+  size_t at = g_stages.size();
+  for (size_t i = 0; i < g_stages.size() && at == g_stages.size(); ++i)
+    if (g_stages[i].device == device && hipEventQuery(g_stages[i].read) == hipSuccess) at = i;
+  if (at == g_stages.size() && g_stages.size() < kMaxStages) {
+    Stage s;
+    s.device = device;
+    g_stages.reserve(kMaxStages);
+    if (hipHostMalloc(reinterpret_cast<void**>(&s.host), kStageBytes, hipHostMallocPortable) != hipSuccess) return nullptr;
+    if (hipEventCreateWithFlags(&s.read, hipEventDisableTiming) != hipSuccess) {
+      (void)hipHostFree(s.host);
+      return nullptr;
+    }
+    g_stages.push_back(s);
+  }
+  for (size_t i = 0; i < g_stages.size() && at == g_stages.size(); ++i)   // wait for the least recent one
+    if (g_stages[i].device == device && hipEventSynchronize(g_stages[i].read) == hipSuccess) at = i;
+  if (at == g_stages.size()) return nullptr;
+  std::rotate(g_stages.begin() + at, g_stages.begin() + at + 1, g_stages.end());
+  return &g_stages.back();
+}
+
+// Enqueue the patches; false if they have to go another way (nothing enqueued).
+bool upload_patches(const std::vector<Patch>& patches, void* image, hipStream_t stream, halo_status_t* status) {
+  const size_t bytes = patches.size() * sizeof(Patch);
+  int device = 0;
+  if (bytes > kStageBytes || hipGetDevice(&device) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lock(g_stage_mu);
+  RelaxedCapture relaxed;
+  Stage* s = free_stage(device);
+  (void)hipGetLastError();
+  if (!s) return false;
+  memcpy(s->host, patches.data(), bytes);
+  hipLaunchKernelGGL(patch_kernel, dim3((patches.size() + 255) / 256), dim3(256), 0, stream,
+                     static_cast<int32_t*>(image), s->host, (int)patches.size());
+  *status = hip_check("metadata patch launch");
+  if (hipEventRecord(s->read, stream) != hipSuccess) (void)hipStreamSynchronize(stream);
+  return true;
 }
 
 halo_status_t upload_bytes(void* dst, const void* src, size_t n, hipStream_t stream) {
@@ -1636,7 +1704,7 @@ extern "C" halo_status_t halo_plan_upload(const halo_plan_t* plan, void* device_
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta needs " + std::to_string(plan->layout.total) + " bytes");
   if ((reinterpret_cast<uintptr_t>(device_meta) & 255) != 0)
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta must be 256-byte aligned");
-  return upload_bytes(device_meta, plan->meta.data(), plan->layout.patches, static_cast<hipStream_t>(stream));
+  return upload_bytes(device_meta, plan->meta.data(), plan->layout.total, static_cast<hipStream_t>(stream));
 }
 
 extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* device_meta,
@@ -1647,28 +1715,24 @@ extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* 
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta needs " + std::to_string(plan->layout.total) + " bytes");
   if ((reinterpret_cast<uintptr_t>(device_meta) & 255) != 0)
     return fail(HALO_ERR_INVALID_ARGUMENT, "device_meta must be 256-byte aligned");
-  // The words an in-place update writes go as patches; where they would be
-  // more bytes than the sections they lie in (between the segment length table
-  // and the row table, in that order in the image), the sections go whole. So
-  // they do into a graph under capture: its replays read the image as it is
-  // then, where a list of patches would be the captured update's.
+  // The words an in-place update writes go as patches; where they are more than
+  // a quarter of the sections they lie in (between the segment length table and
+  // the row table, in that order in the image: the planner's max_patches), the
+  // sections go whole. So they do into a graph under capture: its replays read
+  // the image as it is then, where a list of patches would be the captured
+  // update's.
   const std::vector<Patch>& patches = plan->append.patches;
   const size_t at = plan->layout.seg_len, end = plan->layout.rows;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t* meta = static_cast<uint8_t*>(device_meta);
-  const size_t bytes = patches.size() * sizeof(Patch);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
-  if (patches.size() > plan->layout.max_patches || bytes >= end - at || capture != hipStreamCaptureStatusNone)
-    return upload_bytes(meta + at, plan->meta.data() + at, end - at, st);
-  if (patches.empty()) return HALO_OK;
-  const halo_status_t rc = upload_bytes(meta + plan->layout.patches, patches.data(), bytes, st);
-  if (rc != HALO_OK) return rc;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(patch_kernel, dim3((patches.size() + 255) / 256), dim3(256), 0, st,
-                     reinterpret_cast<int32_t*>(meta), reinterpret_cast<const Patch*>(meta + plan->layout.patches),
-                     (int)patches.size());
-  return hip_check("metadata patch launch");
+  if (patches.size() <= plan->layout.max_patches && capture == hipStreamCaptureStatusNone) {
+    if (patches.empty()) return HALO_OK;
+    halo_status_t rc = HALO_OK;
+    if (upload_patches(patches, meta, st, &rc)) return rc;
+  }
+  return upload_bytes(meta + at, plan->meta.data() + at, end - at, st);
 }
 
 extern "C" halo_status_t halo_prefix_attn_decode(const halo_plan_t* plan, const void* device_meta,

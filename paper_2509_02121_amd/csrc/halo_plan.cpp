@@ -1173,9 +1173,9 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   auto is_tail = [&](const Span& sp) {
     return refs[sp.seg] == 1 ? sp.key_end > tail_lo[sp.seg] : sp.key_end == f.seg_len[sp.seg];
   };
-  // Room for the patches of the segments that can change: a length, the pages
-  // of the spans that can and of the growth reserve, and per such span its end,
-  // the inline copy of it and the record's page ids.
+  // The most patches of the segments that can change: a length, the pages of
+  // the spans that can and of the growth reserve, and per such span its end, the
+  // inline copy of it and the record's page ids.
   if (!prefill) {
     for (const Span& sp : spans)
       if (refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg])
@@ -1193,7 +1193,6 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     // (an update that needs more uploads the sections whole)
     L.max_patches = std::min(L.max_patches, (L.rows - L.seg_len) / 4 / sizeof(Patch));
   }
-  L.patches = place(sizeof(Patch) * L.max_patches);
   L.total = off;
   plan->layout = L;
   // (the image is not zero-filled first: each array is copied in and the
@@ -1223,7 +1222,6 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         {L.whole_items, whole_items.data(), sizeof(Item) * whole_items.size()},
         {L.whole_recs, whole_recs.data(), sizeof(ItemRec) * whole_recs.size()},
         {L.whole_wide, whole_witems.data(), sizeof(Item) * whole_witems.size()},
-        {L.patches, nullptr, 0},
     };
     const size_t n = sizeof(parts) / sizeof(parts[0]);
     for (size_t i = 0; i < n; ++i) {

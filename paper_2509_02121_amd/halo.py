@@ -696,16 +696,22 @@ class PrefixAttention:
     run already enqueued that read that buffer; a run waits for its buffer's
     upload. After an in-place update only what it changed is copied.
 
-    The upload goes on a copy stream of its own, where it overlaps the current
-    step's kernels, or, for forests of up to IN_ORDER_KV_BYTES of K and V, on
-    the current stream: their steps are bound by the host, which a run's wait
-    for another stream costs 25-45 us, and the GPU is idle for the 10-15 us of
-    the copy in order. Measured (us a step, in order and on the copy stream):
-    80 MB 57 and 100, 196 MB 48 and 97; 570 MB 162 and 148.
+    The upload goes on a copy stream of its own: it is behind no other work
+    there and overlaps the current step's kernels, but the next run's wait for
+    it costs the host 15-20 us. It goes on the current stream, where it takes
+    the GPU about 10 us, if the host is what bounds the steps (the last upload
+    had ended by the time of this one), the forest is of up to
+    IN_ORDER_KV_BYTES of K and V, and every call of this object so far was on
+    that stream (so that no run waits for work that it would not be behind
+    anyway). Measured, us a step, by this rule, always in order and always on
+    the copy stream: 57 MB, one call a step 38, 43 and 49, beside 180 us of
+    other work 201, 219 and 194; 196 MB, 32 calls 1029, 1020 and 1085; 570 MB,
+    one call 131, 139 and 131.
     """
 
     IN_ORDER_KV_BYTES = 256 << 20
-    IN_ORDER_META_BYTES = 1 << 20   # of a whole plan's metadata (a new plan)
+    # of a whole plan's metadata (a new plan)
+    IN_ORDER_META_BYTES = 1 << 20
     MAX_WORKSPACES = 16
 
     def __init__(self, params, csr, device="cuda", options=None):
@@ -732,6 +738,11 @@ class PrefixAttention:
         self._bound = [set(), set()]
         self._uploaded = [None, None]
         self._upload_streams = [None, None]
+        # streams that wait for buffer i's upload already
+        self._waited = [set(), set()]
+        # the one stream of this object's calls so far (None: no call yet;
+        # False: calls on several)
+        self._only_stream = None
         # events kept for reuse: of buffer i's uploads, and of its runs by stream
         self._upload_events = [torch.cuda.Event(), torch.cuda.Event()]
         self._run_events = [{}, {}]
@@ -768,18 +779,21 @@ class PrefixAttention:
         ev.record(stream)
         self._uploaded[i] = ev
         self._upload_streams[i] = stream
+        self._waited[i].clear()
 
     def update(self, csr, stream=None):
         """Bring the plan up to date with `csr` (the next decode step's
         forest): the length update when it applies, else a new plan (with
         larger metadata and workspace buffers if needed). Uploads the new
         metadata into the other buffer, on `stream` (None: the current stream
-        for small forests, else this object's copy stream). Callables from
-        bind() keep the plan they were bound with: bind again after update().
-        Returns True if the update applied."""
+        or this object's copy stream, see the class). Callables from bind()
+        keep the plan they were bound with: bind again after update(). Returns
+        True if the update applied."""
         import torch
-        # the last upload read the host image asynchronously
-        self._uploaded[self._cur].synchronize()
+        # the last upload may read the host image asynchronously
+        ahead = self._uploaded[self._cur].query()
+        if not ahead:
+            self._uploaded[self._cur].synchronize()
         applied = self.plan.update_lengths(csr)
         nxt = 1 - self._cur
         if not applied:
@@ -792,8 +806,10 @@ class PrefixAttention:
             stream = self._copy_stream
             small = self.plan.kv_bytes <= self.IN_ORDER_KV_BYTES and (
                 self._holds[nxt] is self.plan or self.plan.device_meta_bytes <= self.IN_ORDER_META_BYTES)
-            if small and not torch.cuda.is_current_stream_capturing():
-                stream = torch.cuda.current_stream(self.device)
+            if ahead and small and self._only_stream and not torch.cuda.is_current_stream_capturing():
+                current = torch.cuda.current_stream(self.device)
+                if current == self._only_stream:
+                    stream = current
         self._upload(nxt, stream)
         self._cur = nxt
         return applied
@@ -803,8 +819,13 @@ class PrefixAttention:
         buffer's upload; returns that stream."""
         import torch
         s = stream if stream is not None else torch.cuda.current_stream(self.device)
-        if s != self._upload_streams[self._cur]:
+        if s != self._upload_streams[self._cur] and s not in self._waited[self._cur]:
             s.wait_event(self._uploaded[self._cur])
+            self._waited[self._cur].add(s)
+        if self._only_stream is None:
+            self._only_stream = s
+        elif self._only_stream is not False and s != self._only_stream:
+            self._only_stream = False
         return s
 
     def _after_run(self, s):

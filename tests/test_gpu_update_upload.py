@@ -109,3 +109,56 @@ def test_removed_tokens_reach_both_buffers(gpu_lib, dtype):
         ro, rl, rows = oracle_for(w)
         w.seg_len = saved
         assert_parity(w, o.double().cpu().numpy(), lse.double().cpu().numpy(), ro, rl, rows, f"cut {cut}")
+
+
+def _small(seed, n_req=3):
+    seg_len = [200] + [330 + 7 * r for r in range(n_req)]
+    return to_device(build_workload("updates", seed, 8, 2, 64, torch.bfloat16, seg_len,
+                                    [[0, 1 + r] for r in range(n_req)], value_scale=0.5))
+
+
+def test_a_decode_on_another_stream_does_not_wait_for_the_current_one(gpu_lib):
+    """The current stream holds long work; a decode loop on a second stream is
+    not behind it, nor is the host that updates the plan."""
+    print("case: update beside long work on the current stream", flush=True)
+    w = _small(94)
+    full = w.forest_csr()
+    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    second = torch.cuda.Stream()
+    cut = [np.array([0] + [c] * 3) for c in (9, 8, 7)]
+    for c in cut:   # both buffers in use
+        pa.update(_shortened(full, w, c))
+        want, _ = pa.run(w.q, w.k_pool, w.v_pool, stream=second)
+    torch.cuda.synchronize()
+    torch.cuda._sleep(400_000_000)   # some 0.2 s
+    long_work = torch.cuda.Event()
+    long_work.record()
+    for c in cut:
+        pa.update(_shortened(full, w, c))
+        got, _ = pa.run(w.q, w.k_pool, w.v_pool, stream=second)
+    second.synchronize()
+    assert not long_work.query(), "the decode waited for the current stream"
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+
+
+def test_uploads_of_many_plans_at_once(gpu_lib):
+    """More uploads in flight than there are staging buffers, on as many
+    streams: each buffer holds what a whole upload gives."""
+    print("case: uploads of many plans", flush=True)
+    w = _small(95)
+    full = w.forest_csr()
+    short = _shortened(full, w, np.array([0, 60, 60, 60]))
+    plans = [halo.Plan.from_csr(params_of(w), short) for _ in range(12)]
+    metas = [torch.empty(p.device_meta_bytes, dtype=torch.uint8, device="cuda") for p in plans]
+    streams = [torch.cuda.Stream() for _ in plans]
+    for p, m in zip(plans, metas):
+        p.upload(m)
+    torch.cuda.synchronize()
+    for cut in (50, 31, 33, 0, 12):
+        for i, (p, m, s) in enumerate(zip(plans, metas, streams)):
+            assert p.update_lengths(_shortened(full, w, np.array([0, cut, (cut + i) % 60, cut])))
+            p.upload_update(m, s)
+    torch.cuda.synchronize()
+    for p, m in zip(plans, metas):
+        assert m.cpu().numpy().tobytes() == p.image()
