@@ -63,8 +63,8 @@ __device__ __forceinline__ int last_at_or_below(const int32_t* indptr, int n, in
 }
 
 // Tiles t_begin .. t_end - 1 by one wave; `stage`: its LDS buffer. The two
-// kinds of loads are two loops: in one, the compiler merges them and drops the
-// non-temporal hint.
+// kinds of loads and stores are two loops: in one, the compiler merges them and
+// drops the non-temporal hint.
 template <typename W, int D, bool STREAM>
 __device__ __forceinline__ void gather_run(const GatherArgs& a, u32x4_t* stage, int first, int64_t t_begin,
                                            int64_t t_end, int lane) {
@@ -121,8 +121,10 @@ __device__ __forceinline__ void gather_run(const GatherArgs& a, u32x4_t* stage, 
     W* dst = out + (a.out_token_offset[seq] + t0) * row + (int64_t)h * D;
     for (int idx = lane; idx < n * VPT; idx += 64) {
       const int tok = idx / VPT, j = idx % VPT;
-      __builtin_nontemporal_store(*reinterpret_cast<const u32x4_t*>(st + tok * ROW + j * E),
-                                  reinterpret_cast<u32x4_t*>(dst + tok * row + j * E));
+      const u32x4_t x = *reinterpret_cast<const u32x4_t*>(st + tok * ROW + j * E);
+      u32x4_t* to = reinterpret_cast<u32x4_t*>(dst + tok * row + j * E);
+      if constexpr (STREAM) __builtin_nontemporal_store(x, to);
+      else *to = x;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -141,13 +143,15 @@ __device__ __forceinline__ void gather_run(const GatherArgs& a, u32x4_t* stage, 
 // vectors hold one dim of E tokens and are split into single words on the
 // way into LDS. W is an unsigned word of the element's width, so every bit
 // pattern (NaN payloads included) moves unchanged. Bound by HBM: tiles are
-// read and rows written once. Rows go past the caches, and so do the tiles of
-// a launch of more than kGatherCached bytes (64 sequences of 256-2048 tokens,
-// K and V, 595 MB: 134 -> 124.4 us, 4.8 TB/s, a device copy's rate). Tiles of
-// smaller launches may be in the last-level cache, which loads past the caches
-// would not use. K and V of 8 MB each, read again / after other work: all
-// cached 9.6 / 17.4 us, only rows past the caches 8.9 / 18.1, both 10.8 / 13.7;
-// of 128 MB each 113 / 137, 95 / 149 and 104 / 110.
+// read and rows written once. A launch of more than kGatherCached bytes reads
+// and writes past the caches (64 sequences of 256-2048 tokens, K and V, 595 MB:
+// 134 -> 124.4 us, 4.8 TB/s, a device copy's rate; 128 MB each, and a copy that
+// reads the rows next: 218 -> 214 us, after other work 241 -> 227). Tiles and
+// rows of smaller launches may stay in the last-level cache, for this call and
+// for the reader of the rows. K and V of 8 / 32 / 60 MB each, gathered and then
+// copied: cached 21.9 / 45.7 / 92.8 us, rows past the caches 22.9 / 50.7 / 102;
+// after other work 24.8 / 66.7 / 128 and 28.5 / 77.4 / 130. (The gather alone,
+// its tiles still cached: 9.3 / 24.8 / 48.3 and 9.3 / 23.8 / 41.4.)
 constexpr int64_t kGatherCached = (int64_t)64 << 20;
 template <typename W, int D>
 __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
