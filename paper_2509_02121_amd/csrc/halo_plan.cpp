@@ -204,7 +204,7 @@ struct ItemSize {
 PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int head_dim, bool wide) {
   constexpr int32_t kMinItem = 16, kMinPiece = 4;        // steps: below, a piece is mostly its start and end
   constexpr int64_t kMaxBytes = (int64_t)256 << 20;      // of partial results
-  // Planning a piece takes the host about 0.4 us, once for all the layers that
+  // Planning a piece takes the host about 0.2 us, once for all the layers that
   // use the plan (tens of calls): of cuts that are about as fast the one of
   // fewer pieces (4 fp32 requests of 64-256 on 1000: 3300 pieces in place of
   // 4400, one of 2 requests 1050 in place of 1980).
@@ -223,7 +223,7 @@ PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int h
   const double row_step = wide ? (d128 ? 0.1 : 0.066) : (d128 ? 2.4 : 1.25);
   const double chain_step = wide ? (d128 ? 0.65 : 0.49) : row_step;
   std::vector<int32_t> ends;
-  std::vector<std::pair<double, int32_t>> parts;   // (CU time, steps)
+  std::vector<float> parts;   // CU times
   std::vector<double> cus;
   const int n_cus = std::max(1, kNumCUs / n_kv_heads);
   const size_t group = wide ? 1 : 4;   // a workgroup's items end together: wide ones are alone in theirs
@@ -238,9 +238,10 @@ PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int h
       cut.ends(x.steps, ends);
       for (size_t k = 0; k < ends.size(); ++k) {
         const int32_t n = ends[k] - (k ? ends[k - 1] : 0);
-        parts.emplace_back(wide ? 2.0 + n * row_step * (1 + (x.rows + 31) / 32) : 3.5 + n * row_step, n);
+        const double t = wide ? 2.0 + n * row_step * (1 + (x.rows + 31) / 32) : 3.5 + n * row_step;
+        parts.push_back((float)t);
         last = std::max(last, (wide ? 5.0 : 3.5) + n * chain_step);
-        sum += parts.back().first;
+        sum += t;
       }
       if (ends.size() > 1) part_rows += (int64_t)ends.size() * x.rows;
     }
@@ -249,11 +250,11 @@ PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int h
     const double rest = (part_rows ? 4.0 + 2.0 * bytes / 8e6 : 0.0) + kHostPiece * parts.size() * n_kv_heads;
     if (bytes > kMaxBytes || std::max(last, 0.999 * sum / (group * n_cus)) + rest >= least)
       return std::numeric_limits<double>::infinity();
-    std::sort(parts.begin(), parts.end(), std::greater<std::pair<double, int32_t>>());
+    std::sort(parts.begin(), parts.end(), std::greater<float>());
     cus.assign(n_cus, 0.0);   // min-heap of the CUs' end times
     for (size_t i = 0; i < parts.size(); i += group) {
       std::pop_heap(cus.begin(), cus.end(), std::greater<double>());
-      cus.back() += parts[i].first;
+      cus.back() += parts[i];
       last = std::max(last, cus.back());
       std::push_heap(cus.begin(), cus.end(), std::greater<double>());
     }
@@ -399,13 +400,16 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     bool shared;
     bool wide;
     int32_t chunk = -1;   // shared items: id of the (piece, kv head) whose pages they read
-    // prefill: rows in prefill_rows (in place of `rows`), and for a piece its
-    // place among the pieces' part_bases
+    // prefill: rows in prefill_rows and spans in prefill_spans (in place of
+    // `rows` and `spans`), the latter shared by the kv heads, and for a piece
+    // its place among the pieces' part_bases
     int32_t row_begin = 0, n_rows = 0, part_at = -1;
+    uint32_t span_begin = 0, n_spans = 0;
   };
   auto& protos = scratch<std::vector<Proto>, 0>();
   auto& prefill_rows = scratch<std::vector<Row>, 1>();
-  std::vector<Proto> whole;   // prefill: the items before they were cut into pieces (empty: not cut)
+  auto& prefill_spans = scratch<std::vector<Span>, 1>();
+  auto& whole = scratch<std::vector<Proto>, 1>();   // prefill: the items before they were cut into pieces (empty: not cut)
   std::vector<MergeItem> merge_items;     // prefill: the items cut into pieces, and each piece's part_base
   std::vector<int32_t> merge_bases;
   int32_t n_chunks = 0;
@@ -609,6 +613,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     plan->wide_group = 1;
     const int rows_per = wide ? (opt.wide_rows > 0 ? opt.wide_rows : kSmallWideRows) : kRowsPerItem;
     plan->small_wide = wide && rows_per <= kSmallWideRows;
+    prefill_rows.resize(n_q_rows * Hq);
+    size_t row_at = 0;
     for (int r = 0; r < R; ++r) {
       const int32_t n = f.q_len[r];
       if (n == 0) continue;
@@ -631,16 +637,20 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         // keys up to the group's first position are visible to every row:
         // that part of the chunk (whole 32-key steps) needs no mask
         const int32_t open = std::min(qmax + 1, (qmin + 1) / 32 * 32);
+        const size_t span_begin = prefill_spans.size();
+        prefill_spans.insert(prefill_spans.end(), prefix_spans.begin(), prefix_spans.end());
+        if (open > 0) prefill_spans.push_back(Span{chunk_seg, 0, open, 0, 0, {0, 0, 0}});
+        if (qmax + 1 > open) prefill_spans.push_back(Span{chunk_seg, open, qmax + 1, 1, 0, {0, 0, 0}});
         for (int g = 0; g < Hkv; ++g) {
           Proto pr;
-          pr.row_begin = (int32_t)prefill_rows.size();
+          pr.row_begin = (int32_t)row_at;
           pr.n_rows = in_block;
-          for (int64_t x = rb; x < rb + in_block; ++x)
-            prefill_rows.push_back(Row{(int32_t)((tok0[r] + x / G) * Hq + g * G + x % G), (int32_t)(x / G), -1, -1});
-          pr.spans.reserve(prefix_spans.size() + 2);
-          pr.spans = prefix_spans;
-          if (open > 0) pr.spans.push_back(Span{chunk_seg, 0, open, 0, 0, {0, 0, 0}});
-          if (qmax + 1 > open) pr.spans.push_back(Span{chunk_seg, open, qmax + 1, 1, 0, {0, 0, 0}});
+          for (int64_t x = rb, i = rb / G, j = rb % G; x < rb + in_block; ++x) {
+            prefill_rows[row_at++] = Row{(int32_t)((tok0[r] + i) * Hq + g * G + j), (int32_t)i, -1, -1};
+            if (++j == G) j = 0, ++i;
+          }
+          pr.span_begin = (uint32_t)span_begin;
+          pr.n_spans = (uint32_t)(prefill_spans.size() - span_begin);
           pr.kv_head = g;
           pr.keys = prefix_keys + qmax + 1;
           pr.shared = false;
@@ -653,8 +663,12 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     // cut their keys into pieces, whose results a second launch merges.
     std::vector<ItemSize> sizes(protos.size() / Hkv);   // of head 0's items
     for (size_t i = 0; i < sizes.size(); ++i) {
+      const Proto& pr = protos[i * Hkv];
       int64_t n = 0;
-      for (const Span& sp : protos[i * Hkv].spans) n += ceil_div(sp.key_end - sp.key_begin, kKeysPerStep);
+      for (uint32_t k = 0; k < pr.n_spans; ++k) {
+        const Span& sp = prefill_spans[pr.span_begin + k];
+        n += ceil_div(sp.key_end - sp.key_begin, kKeysPerStep);
+      }
       sizes[i] = ItemSize{(int32_t)std::min<int64_t>(n, std::numeric_limits<int32_t>::max()), protos[i * Hkv].n_rows};
     }
     const PieceCut cut = (wide && !plan->small_wide) || (!wide && p.kv_dtype == HALO_BF16)
@@ -666,45 +680,48 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       std::vector<int32_t> ends;
       for (size_t i = 0; i < whole.size(); i += Hkv) {
         cut.ends(sizes[i / Hkv].steps, ends);
-        for (size_t k = 0; k < ends.size(); ++k)
+        if (ends.size() == 1) {
+          for (int g = 0; g < Hkv; ++g) protos.push_back(whole[i + g]);
+          continue;
+        }
+        for (size_t k = 0; k < ends.size(); ++k) {
+          // the keys of steps lo .. hi - 1, the same for all heads
+          const uint32_t span_begin = (uint32_t)prefill_spans.size();
+          int64_t keys = 0, at = 0;   // at: first step of a span
+          const int64_t lo = k ? ends[k - 1] : 0, hi = ends[k];
+          for (uint32_t x = 0; x < whole[i].n_spans; ++x) {
+            Span piece = prefill_spans[whole[i].span_begin + x];
+            const int64_t n = ceil_div(piece.key_end - piece.key_begin, kKeysPerStep);
+            const int64_t a = std::max(lo, at), b = std::min(hi, at + n);
+            if (a < b) {
+              piece.key_end = (int32_t)std::min<int64_t>(piece.key_end, piece.key_begin + (b - at) * kKeysPerStep);
+              piece.key_begin = (int32_t)(piece.key_begin + (a - at) * kKeysPerStep);
+              keys += paged(piece.key_end - piece.key_begin);
+              prefill_spans.push_back(piece);
+            }
+            at += n;
+          }
           for (int g = 0; g < Hkv; ++g) {
-            const Proto& w = whole[i + g];
-            if (ends.size() == 1) {
-              protos.push_back(w);
-              continue;
-            }
             Proto pr;
-            pr.row_begin = w.row_begin;
-            pr.n_rows = w.n_rows;
-            pr.kv_head = w.kv_head;
+            pr.row_begin = whole[i + g].row_begin;
+            pr.n_rows = whole[i + g].n_rows;
+            pr.kv_head = g;
             pr.shared = false;
-            pr.wide = w.wide;
+            pr.wide = wide;
             pr.part_at = (int32_t)(merge_bases.size() + g * ends.size() + k);
-            pr.keys = 0;
-            int64_t at = 0;   // first step of a span
-            const int64_t lo = k ? ends[k - 1] : 0, hi = ends[k];
-            for (const Span& sp : w.spans) {
-              const int64_t n = ceil_div(sp.key_end - sp.key_begin, kKeysPerStep);
-              const int64_t a = std::max(lo, at), b = std::min(hi, at + n);
-              if (a < b) {
-                Span piece = sp;
-                piece.key_begin = (int32_t)(sp.key_begin + (a - at) * kKeysPerStep);
-                piece.key_end = (int32_t)std::min<int64_t>(sp.key_end, sp.key_begin + (b - at) * kKeysPerStep);
-                pr.keys += paged(piece.key_end - piece.key_begin);
-                pr.spans.push_back(piece);
-              }
-              at += n;
-            }
+            pr.span_begin = span_begin;
+            pr.n_spans = (uint32_t)prefill_spans.size() - span_begin;
+            pr.keys = keys;
             protos.push_back(std::move(pr));
           }
-        if (ends.size() > 1)
-          for (int g = 0; g < Hkv; ++g) {
-            merge_items.push_back(MergeItem{whole[i + g].row_begin, whole[i + g].n_rows, (int32_t)merge_bases.size(),
-                                            (int32_t)ends.size()});
-            merge_bases.resize(merge_bases.size() + ends.size());
-            plan->merge_item_rows = std::max(plan->merge_item_rows, whole[i + g].n_rows);
-            plan->merged_rows += whole[i + g].n_rows;
-          }
+        }
+        for (int g = 0; g < Hkv; ++g) {
+          merge_items.push_back(MergeItem{whole[i + g].row_begin, whole[i + g].n_rows, (int32_t)merge_bases.size(),
+                                          (int32_t)ends.size()});
+          merge_bases.resize(merge_bases.size() + ends.size());
+          plan->merge_item_rows = std::max(plan->merge_item_rows, whole[i + g].n_rows);
+          plan->merged_rows += whole[i + g].n_rows;
+        }
       }
     }
   }
@@ -808,6 +825,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   auto& parts_fill = scratch<std::vector<int32_t>, 5>();
   parts_fill.assign(prefill ? 0 : n_q_rows * Hq, 0);
   int64_t part_rows = 0;
+  struct { int64_t proto_begin; int32_t begin, count; } last_spans = {-1, 0, 0};
   // One proto as an item: appended to `wide_out` or to `out` and `chunk_out`.
   auto emit = [&](const Proto& pr, bool final_item, std::vector<Item>& out, std::vector<int32_t>& chunk_out,
                   std::vector<Item>& wide_out) {
@@ -837,6 +855,9 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     }
     if (pr.shared) plan->n_shared_items++;
     rows.insert(rows.end(), pr.rows.begin(), pr.rows.end());
+    // (the kv heads of a prefill's row block follow each other and share spans)
+    const bool same_spans = prefill && last_spans.proto_begin == (int64_t)pr.span_begin;
+    if (same_spans) it.span_begin = last_spans.begin;
     // Split spans: a narrow item's first span at kNarrowSpanKeys (its page
     // ids travel in the item's record), every other span at kMaxSpanKeys
     // (its page ids fill one 64-lane register); resolve their page slots.
@@ -845,7 +866,10 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     // two, the second part being a later span), so that
     // halo_plan_update_lengths can grow it in place. The cut looks at whole
     // pages only.
-    for (const Span& sp : pr.spans) {
+    const Span* sp_begin = prefill ? prefill_spans.data() + pr.span_begin : pr.spans.data();
+    const Span* sp_end = sp_begin + (same_spans ? 0 : prefill ? pr.n_spans : pr.spans.size());
+    for (const Span* spp = sp_begin; spp != sp_end; ++spp) {
+      const Span& sp = *spp;
       const bool tail = !prefill && refs[sp.seg] == 1 && sp.key_end == f.seg_len[sp.seg];
       const int32_t room = tail ? reserve : 0;
       for (int64_t kb = sp.key_begin; kb < sp.key_end;) {
@@ -863,7 +887,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         kb += take;
       }
     }
-    it.n_spans = (int32_t)spans.size() - it.span_begin;
+    it.n_spans = same_spans ? last_spans.count : (int32_t)spans.size() - it.span_begin;
+    if (prefill) last_spans = {pr.span_begin, it.span_begin, it.n_spans};
     if (it.n_spans > 0) {
       const Span& s0 = spans[it.span_begin];
       it.s0_key_begin = s0.key_begin;
@@ -963,10 +988,10 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   //    longest first and fill the open workgroup of their XCD (shared) or
   //    of the XCD with the fewest items (private). Workgroups then launch
   //    longest first, and the short ones fill the tail.
-  // Returns the number of workgroups, items and recs in slot order; -1 with
-  // the error set.
-  auto deal = [&](std::vector<Item>& items, const std::vector<int32_t>& item_chunk, size_t n_wide,
-                  std::vector<ItemRec>& recs) -> int64_t {
+  // Returns the number of workgroups, and in at_slot the item of each slot (-1:
+  // none); -1 with the error set.
+  auto deal = [&](const std::vector<Item>& items, const std::vector<int32_t>& item_chunk, size_t n_wide,
+                  std::vector<int32_t>& at_slot) -> int64_t {
     if (items.empty()) return 0;
     const int waves = narrow_items_per_block(p.kv_dtype);
     const int64_t n = (int64_t)items.size();
@@ -1083,36 +1108,40 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         }
       }
     }
-    // slot layout, empty slots n_rows = 0; and each slot's lane record
-    auto& dealt = scratch<std::vector<Item>, 2>();
-    dealt.assign((size_t)(nb * slots), Item{});
-    recs.assign((size_t)(nb * slots), ItemRec{});
-    for (int64_t b = 0; b < nb; ++b)
-      for (int32_t k = 0; k < count[b]; ++k) {
-        const size_t at = (size_t)(b * slots) + k;
-        const Item& it = items[blk[b * cap + k]];
-        dealt[at] = it;
-        ItemRec& rc = recs[at];
+    at_slot.assign((size_t)(nb * slots), -1);
+    for (int64_t b = 0; b < nb; ++b) std::copy_n(blk.begin() + b * cap, count[b], at_slot.begin() + b * slots);
+    plan->narrow_slots = slots;
+    return nb;
+  };
+  // The items in their slots, and each slot's lane record, into the image.
+  auto fill_slots = [&](const std::vector<Item>& items, const std::vector<int32_t>& at_slot, uint8_t* items_at,
+                        uint8_t* recs_at) {
+    for (size_t at = 0; at < at_slot.size(); ++at) {
+      Item it{};   // (empty: n_rows = 0)
+      ItemRec rc{};
+      if (at_slot[at] >= 0) {
+        it = items[at_slot[at]];
+        const Row* row = rows.data() + it.row_begin;
+        const bool slots = !prefill && it.part_base >= 0;
         for (int r = 0; r < 16; ++r) {
-          rc.q_row[r] = r < it.n_rows ? rows[it.row_begin + r].q_row : -1;
-          rc.aux[r] = r >= it.n_rows ? 0 : !prefill && it.part_base >= 0 ? rows[it.row_begin + r].slot
-                                                             : rows[it.row_begin + r].qpos;
+          rc.q_row[r] = r < it.n_rows ? row[r].q_row : -1;
+          rc.aux[r] = r >= it.n_rows ? 0 : slots ? row[r].slot : row[r].qpos;
         }
         if (it.n_spans > 0) {
           const Span& s0 = spans[it.span_begin];
           const int32_t np = (s0.key_end - s0.key_begin + p.page_size - 1) / p.page_size;
-          for (int32_t j = 0; j < np && j < 32; ++j) rc.page[j] = page_slots[s0.page_off + j];
+          memcpy(rc.page, page_slots.data() + s0.page_off, sizeof(int32_t) * std::min(np, 32));
         }
       }
-    items.swap(dealt);
-    plan->narrow_slots = slots;
-    return nb;
+      memcpy(items_at + at * sizeof(Item), &it, sizeof(Item));
+      memcpy(recs_at + at * sizeof(ItemRec), &rc, sizeof(ItemRec));
+    }
   };
-  auto& recs = scratch<std::vector<ItemRec>, 0>();
-  auto& whole_recs = scratch<std::vector<ItemRec>, 1>();
+  auto& at_slot = scratch<std::vector<int32_t>, 23>();
+  auto& whole_at_slot = scratch<std::vector<int32_t>, 24>();
   const int64_t n_real_items = (int64_t)items.size();
-  const int64_t nb_main = deal(items, item_chunk, witems.size(), recs);
-  const int64_t nb_whole = nb_main < 0 ? -1 : deal(whole_items, whole_chunk, whole_witems.size(), whole_recs);
+  const int64_t nb_main = deal(items, item_chunk, witems.size(), at_slot);
+  const int64_t nb_whole = nb_main < 0 ? -1 : deal(whole_items, whole_chunk, whole_witems.size(), whole_at_slot);
   if (nb_whole < 0) {
     delete plan;
     return HALO_ERR_INVALID_ARGUMENT;
@@ -1151,8 +1180,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   L.seg_page_off = place(sizeof(int32_t) * std::max(S, 1));
   L.seg_len = place(sizeof(int32_t) * std::max(S, 1));
   L.page_ids = place(sizeof(int32_t) * std::max<int64_t>(total_pages, 1));
-  L.items = place(sizeof(Item) * std::max<size_t>(items.size(), 1));
-  L.item_recs = place(sizeof(ItemRec) * std::max<size_t>(recs.size(), 1));
+  L.items = place(sizeof(Item) * std::max<size_t>(at_slot.size(), 1));
+  L.item_recs = place(sizeof(ItemRec) * std::max<size_t>(at_slot.size(), 1));
   L.wide_items = place(sizeof(Item) * std::max<size_t>(witems.size(), 1));
   L.spans = place(sizeof(Span) * std::max<size_t>(spans.size(), 1));
   L.rows = place(sizeof(Row) * std::max<size_t>(rows.size(), 1));
@@ -1161,8 +1190,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
   L.merge_parts = place(sizeof(int32_t) * std::max<size_t>(merge_parts.size(), 1));
   L.merge_items = place(sizeof(MergeItem) * merge_items.size());
   L.merge_bases = place(sizeof(int32_t) * merge_bases.size());
-  L.whole_items = place(sizeof(Item) * whole_items.size());
-  L.whole_recs = place(sizeof(ItemRec) * whole_recs.size());
+  L.whole_items = place(sizeof(Item) * whole_at_slot.size());
+  L.whole_recs = place(sizeof(ItemRec) * whole_at_slot.size());
   L.whole_wide = place(sizeof(Item) * whole_witems.size());
   // A decode plan's private segment can be shortened in place to more than
   // tail_lo keys: the first key of its last span, or, where the planner's chunks
@@ -1209,8 +1238,8 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         {L.seg_page_off, slot_off.data(), S ? sizeof(int32_t) * S : 0},
         {L.seg_len, f.seg_len, S ? sizeof(int32_t) * S : 0},
         {L.page_ids, page_slots.data(), sizeof(int32_t) * (size_t)total_pages},
-        {L.items, items.data(), sizeof(Item) * items.size()},
-        {L.item_recs, recs.data(), sizeof(ItemRec) * recs.size()},
+        {L.items, nullptr, sizeof(Item) * at_slot.size()},
+        {L.item_recs, nullptr, sizeof(ItemRec) * at_slot.size()},
         {L.wide_items, witems.data(), sizeof(Item) * witems.size()},
         {L.spans, spans.data(), sizeof(Span) * spans.size()},
         {L.rows, rows.data(), sizeof(Row) * rows.size()},
@@ -1219,16 +1248,18 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         {L.merge_parts, merge_parts.data(), sizeof(int32_t) * merge_parts.size()},
         {L.merge_items, merge_items.data(), sizeof(MergeItem) * merge_items.size()},
         {L.merge_bases, merge_bases.data(), sizeof(int32_t) * merge_bases.size()},
-        {L.whole_items, whole_items.data(), sizeof(Item) * whole_items.size()},
-        {L.whole_recs, whole_recs.data(), sizeof(ItemRec) * whole_recs.size()},
+        {L.whole_items, nullptr, sizeof(Item) * whole_at_slot.size()},
+        {L.whole_recs, nullptr, sizeof(ItemRec) * whole_at_slot.size()},
         {L.whole_wide, whole_witems.data(), sizeof(Item) * whole_witems.size()},
     };
     const size_t n = sizeof(parts) / sizeof(parts[0]);
     for (size_t i = 0; i < n; ++i) {
       const size_t end = i + 1 < n ? parts[i + 1].at : L.total;
-      if (parts[i].bytes) memcpy(m + parts[i].at, parts[i].src, parts[i].bytes);
+      if (parts[i].src && parts[i].bytes) memcpy(m + parts[i].at, parts[i].src, parts[i].bytes);
       memset(m + parts[i].at + parts[i].bytes, 0, end - parts[i].at - parts[i].bytes);
     }
+    fill_slots(items, at_slot, m + L.items, m + L.item_recs);
+    fill_slots(whole_items, whole_at_slot, m + L.whole_items, m + L.whole_recs);
   }
 
   // What halo_plan_update_lengths needs: the forest the plan was built for,
@@ -1248,11 +1279,11 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     ax.refs = refs;
     ax.page_slot_off = slot_off;
     std::vector<int64_t> first_of(spans.size(), -1), rec_of(spans.size(), -1);
-    for (size_t i = 0; i < items.size(); ++i)
-      if (items[i].n_rows > 0 && items[i].n_spans > 0) {
-        first_of[items[i].span_begin] = (int64_t)(L.items + i * sizeof(Item));
-        rec_of[items[i].span_begin] = (int64_t)(L.item_recs + i * sizeof(ItemRec));
-      }
+    for (size_t at = 0; at < at_slot.size(); ++at) {
+      if (at_slot[at] < 0 || items[at_slot[at]].n_spans == 0) continue;
+      first_of[items[at_slot[at]].span_begin] = (int64_t)(L.items + at * sizeof(Item));
+      rec_of[items[at_slot[at]].span_begin] = (int64_t)(L.item_recs + at * sizeof(ItemRec));
+    }
     for (size_t i = 0; i < witems.size(); ++i)
       if (witems[i].n_spans > 0) first_of[witems[i].span_begin] = (int64_t)(L.wide_items + i * sizeof(Item));
     ax.tail_indptr.assign(S + 1, 0);

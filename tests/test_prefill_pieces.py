@@ -59,3 +59,25 @@ def test_pieces_tile_the_visible_keys(seed):
     assert st["num_partial_rows"] == n_slots and (st["num_merge_rows"] > 0) == (n_slots > 0)
     pad = lambda x: -(-x // 256) * 256
     assert plan.workspace_bytes == (pad(n_slots * 64 * 4) + pad(n_slots * 4) if n_slots else 0)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_kv_heads_share_their_spans(dtype):
+    """The spans of a row block are listed once for all kv heads, cut into
+    pieces or not: they are most of what the planner writes."""
+    for q_len in ([64], [900, 3], [1] * 40):
+        seg_len = [1500] + q_len
+        paths = [[0, 1 + r] for r in range(len(q_len))]
+        n = {}
+        for h in (1, 8):
+            params = halo.make_params(4 * h, h, 128, dtype, 1 << 16, 0.1)
+            pages = [(x + 15) // 16 for x in seg_len]
+            indptr = np.concatenate([[0], np.cumsum(pages)]).astype(np.int32)
+            plan = halo.Plan(params, seg_len, indptr, np.arange(indptr[-1]), np.arange(len(q_len) + 1) * 2,
+                             np.concatenate(paths), q_len)
+            m = plan.inspect()
+            items = np.concatenate([m["items"].reshape(-1, 16), m["wide_items"].reshape(-1, 16)])
+            items = items[items[:, 1] > 0]
+            assert len(m["spans"]) <= items[items[:, 4] == 0][:, 3].sum() * 2   # (with the uncut items')
+            n[h] = len({(int(x[2]), int(x[3])) for x in items}), (items[:, 4] == 0).sum()
+        assert n[1][0] == n[1][1] and n[8][0] == n[8][1]
