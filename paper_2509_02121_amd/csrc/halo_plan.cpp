@@ -197,7 +197,9 @@ struct ItemSize {
 // 0.1 per 32 rows and step, whether one workgroup or two share it; a lone
 // item's chain takes 5 + 0.65 per step (d 64: 0.66 and 0.75 of that per step).
 // fp32 items, four to a workgroup and one per SIMD: 3.5 + 2.4 per step (d 64:
-// 1.25). The merge launch takes 4, and the partial results, fp32, written and
+// 1.25; there a CU has the registers for a second workgroup, but two are no
+// faster than one after the other: 4792 items of some 35 steps take 1.4 per step
+// and SIMD, a lone chain 1.36). The merge launch takes 4, and the partial results, fp32, written and
 // read, move at 8 TB/s. Measured, uncut and cut: one request of 901 tokens on
 // 4999 cached ones 121 -> 102, of 64 on 5000 105 -> 23, of 8 on 5000 89 -> 15;
 // fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181 -> 136.
@@ -209,7 +211,7 @@ PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int h
   // fewer pieces (4 fp32 requests of 64-256 on 1000: 3300 pieces in place of
   // 4400, one of 2 requests 1050 in place of 1980).
   constexpr double kHostPiece = 0.005;
-  const int64_t per_cu = wide ? 2 : 4;                   // items a CU holds at once
+  const int64_t per_cu = wide ? 2 : 4;                   // items a CU works off at once
   int64_t total = 0;
   int32_t longest = 0;
   for (const ItemSize& x : items) {
