@@ -199,10 +199,11 @@ struct ItemSize {
 // fp32 items, four to a workgroup and one per SIMD: 3.5 + 2.4 per step (d 64:
 // 1.25; there a CU has the registers for a second workgroup, but two are no
 // faster than one after the other: 4792 items of some 35 steps take 1.4 per step
-// and SIMD, a lone chain 1.36). The merge launch takes 4, and the partial results, fp32, written and
-// read, move at 8 TB/s. Measured, uncut and cut: one request of 901 tokens on
-// 4999 cached ones 121 -> 102, of 64 on 5000 105 -> 23, of 8 on 5000 89 -> 15;
-// fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181 -> 136.
+// and SIMD, a lone chain 1.36). The merge launch takes 4, and the partial
+// results, fp32, written and read, move at 8 TB/s. Measured, uncut and cut: one
+// request of 901 tokens on 4999 cached ones 121 -> 102, of 64 on 5000 105 -> 23,
+// of 8 on 5000 89 -> 15; fp32, of 64 on 2000 159 -> 38, 4 of 64-256 on 1000 181
+// -> 136.
 PieceCut choose_pieces(const std::vector<ItemSize>& items, int n_kv_heads, int head_dim, bool wide) {
   constexpr int32_t kMinItem = 16, kMinPiece = 4;        // steps: below, a piece is mostly its start and end
   constexpr int64_t kMaxBytes = (int64_t)256 << 20;      // of partial results

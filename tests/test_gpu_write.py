@@ -110,16 +110,10 @@ def test_scatter_long_ranges_among_appends(gpu_lib, n_seqs, dtype, D, kind):
     assert np.array_equal(got, exp)
 
 
-@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.float32, 64)])
-def test_scatter_kv_equals_two_single_pool_calls(gpu_lib, dtype, D):
-    """The two-pool call writes exactly what the two single-pool calls write,
-    also with a flagged sequence among the good ones."""
-    print(f"case: scatter_kv {dtype} d{D}", flush=True)
-    rng = np.random.default_rng(21 + D)
-    H, n_pool = 3, 64
+def _kv_call_and_two_single_calls(dtype, D, H, n_pool, seqs, rng):
+    """The pools after one two-pool call equal those after two single-pool
+    calls, and both flag the same; returns the flag."""
     ity = _int_type(dtype)
-    seqs, spare = _random_seqs(rng, n_pool, 12, 4)
-    seqs.append((spare[:1], 9, 8))                       # 9 + 8 > 16: flagged, skipped
     total = sum(c for _, _, c in seqs)
     dev = "cuda"
     pools = [_random_bits((n_pool * H * PAGE * D,), ity, rng).to(dev).view(dtype) for _ in range(2)]
@@ -132,15 +126,50 @@ def test_scatter_kv_equals_two_single_pool_calls(gpu_lib, dtype, D):
              torch.as_tensor(np.array([c for _, _, c in seqs], np.int32), device=dev),
              torch.as_tensor(offs, device=dev))
     params = halo.make_params(H, H, D, dtype, n_pool, 0.125, dtype)
+    before = [p.clone() for p in pools]
     single = [p.clone() for p in pools]
     flags = torch.zeros(2, dtype=torch.int32, device=dev)
     halo.kv_page_scatter(single[0], params, halo.HALO_POOL_K, *lists, ins[0], flags[0:1])
     halo.kv_page_scatter(single[1], params, halo.HALO_POOL_V, *lists, ins[1], flags[0:1])
     halo.kv_page_scatter_kv(pools[0], pools[1], params, *lists, ins[0], ins[1], flags[1:2])
     torch.cuda.synchronize()
-    assert flags.tolist() == [1, 1]
-    for a, b in zip(pools, single):
-        assert torch.equal(a.view(ity), b.view(ity))
+    assert flags[0] == flags[1]
+    for a, b, c in zip(pools, single, before):
+        assert torch.equal(a.view(ity), b.view(ity)) and not torch.equal(a.view(ity), c.view(ity))
+    return int(flags[0])
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.float32, 64)])
+def test_scatter_kv_equals_two_single_pool_calls(gpu_lib, dtype, D):
+    """The two-pool call writes exactly what the two single-pool calls write,
+    also with a flagged sequence among the good ones."""
+    print(f"case: scatter_kv {dtype} d{D}", flush=True)
+    rng = np.random.default_rng(21 + D)
+    seqs, spare = _random_seqs(rng, 64, 12, 4)
+    seqs.append((spare[:1], 9, 8))                       # 9 + 8 > 16: flagged, skipped
+    assert _kv_call_and_two_single_calls(dtype, D, 3, 64, seqs, rng) == 1
+
+
+@pytest.mark.parametrize("n_seqs", [64, 65, 300, 4100])
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.float32, 128)])
+def test_scatter_kv_of_many_sequences(gpu_lib, n_seqs, dtype, D):
+    """Two pools at the batch sizes where the whole pages are summed by a wave,
+    by a workgroup (several sequences per thread past 256) and in two groups
+    (past 4096), the chunks with whole pages in different threads' sequences;
+    with and without a sequence whose range does not fit its pages."""
+    print(f"case: scatter_kv {n_seqs} sequences {dtype} d{D}", flush=True)
+    rng = np.random.default_rng(n_seqs + D)
+    chunks = {0: (5, 100), 1: (0, 16), n_seqs // 2: (16, 48), n_seqs // 2 + 1: (15, 33), n_seqs - 1: (3, 77)}
+    perm = rng.permutation(n_seqs + 60).astype(np.int32)
+    seqs, at = [], 0
+    for i in range(n_seqs):
+        start, count = chunks.get(i, (int(rng.integers(0, PAGE)), int(rng.integers(0, 2))))
+        n = max(1, (start + count + PAGE - 1) // PAGE)
+        seqs.append((perm[at:at + n], start, count))
+        at += n
+    assert _kv_call_and_two_single_calls(dtype, D, 3, len(perm), seqs, rng) == 0
+    seqs[n_seqs // 3] = (seqs[n_seqs // 3][0], 9, 8)
+    assert _kv_call_and_two_single_calls(dtype, D, 3, len(perm), seqs, rng) == 1
 
 
 def test_scatter_then_gather_round_trip(gpu_lib):
