@@ -840,9 +840,9 @@ def measure_workload(name, args, dev, pool_fill=0.0, with_cpu=False, percentiles
 
     kernels = []
     if stats["num_wide_items"] or stats["num_items"]:
-        kernels.append("attn_kernel")
+        kernels.append("wide_kernel" if w.is_prefill and stats["num_wide_items"] else "attn_kernel")
     if stats["num_merge_rows"]:
-        kernels.append("merge_kernel")
+        kernels.append("merge_items_kernel" if w.is_prefill else "merge_kernel")
     kernel_desc = " + ".join(kernels) + (" (one library call; time = all of its kernels)" if len(kernels) > 1 else "")
 
     if w.is_prefill:

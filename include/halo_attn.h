@@ -108,7 +108,7 @@ typedef struct halo_plan halo_plan_t;
 /* Validate a forest and build the work lists of one batch step.
  * On success *plan is set, *device_meta_bytes is the size of the device
  * buffer halo_plan_upload fills, and *workspace_bytes the scratch the run
- * call needs (0 for prefill). Host arrays are copied; the caller may free
+ * call uses (0 where no row has partial results). Host arrays are copied; the caller may free
  * them on return. Returns INVALID_ARGUMENT / UNSUPPORTED with a message on
  * any malformed or unsupported input; *plan is then NULL. */
 halo_status_t halo_plan_create(const halo_attn_params_t* params,
@@ -121,15 +121,17 @@ halo_status_t halo_plan_create(const halo_attn_params_t* params,
  * the planner from the batch"). The result never depends on these: any
  * valid setting gives the same attention, up to summation order.
  *   kc_shared        keys per chunk of a shared segment in narrow items
- *                    (multiple of 32, <= 1024; 0: 512)
+ *                    (multiple of 32, <= 1024; 0: 512, or as few as 64 for
+ *                    small batches)
  *   kc_private       keys per chunk of a request's private keys (multiple of
  *                    32, <= 65536; 0: 2048, 1024, 512 or 256, the longest
- *                    that leaves >= 3 items per CU)
+ *                    that leaves >= 3 items per CU, or as few as 64 for small
+ *                    batches)
  *   wide             -1: wide items (256-row MFMA workgroups over one key
  *                    stream) when the shared work is large; 0: never; 1:
  *                    always (bf16 only)
  *   wide_rows        rows per wide item (multiple of 32, <= 256; 0: from the
- *                    sharing groups' sizes; prefill: 256)
+ *                    sharing groups' sizes; prefill: 128)
  *   kc_wide          keys per chunk of a shared segment in wide items
  *                    (multiple of 32; 0: the longest of 4096, 2048, ... that
  *                    gives >= wide_min_items items)

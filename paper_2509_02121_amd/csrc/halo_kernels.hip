@@ -376,8 +376,9 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, const Item& it, cons
   // an offset that never changes; its loads differ only in their immediate
   // offsets (K: +1 KB per 32 dims, +128 for keys 8-15; V: +512 per 16 dims).
   // With an address worked out for every load: Llama-8B-shaped decode 22.1 ->
-  // 21.7 us, 4 requests of 12000-24000 keys 54.2 -> 53.2, two-level tree at d
-  // 64 64.6 -> 64.1. (fp32, bound by its products, lost 3% to it.)
+  // 21.7 us, 4 requests of 12000-24000 keys 54.2 -> 53.2; calls that HBM bounds
+  // the same (two-level tree at d 64 64.3 us, 70B-shaped batch within its noise).
+  // (fp32, bound by its products, lost 3% to it.)
   // A position past the item's end loads, in every lane, the same one of 16
   // distinct 16-byte words at the start of the item table (at least 8
   // workgroups x 8 slots x 64 bytes; cached after its first use) instead of

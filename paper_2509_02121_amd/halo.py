@@ -770,6 +770,8 @@ class PrefixAttention:
                 stream.wait_stream(u)
         self._runs[i].clear()
         self._bound[i].clear()
+        if len(self._run_events[i]) > self.MAX_WORKSPACES:   # (streams come and go)
+            self._run_events[i].clear()
         if self._holds[i] is self.plan:
             self.plan.upload_update(self._metas[i], stream)
         else:
