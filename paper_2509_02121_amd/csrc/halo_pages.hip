@@ -194,7 +194,8 @@ struct ScatterArgs {
   int32_t num_seqs;
   int32_t num_kv_heads;
   int32_t n_pairs;
-  int32_t seq_blocks;    // workgroups by sequence and pool (partly touched pages)
+  int32_t seq_blocks;    // workgroups by sequence (partly touched pages)
+  int32_t seq_split;     // of them per sequence: 1, or one for each pool
   int32_t tile_blocks;   // workgroups per pool for the whole pages' tiles
 };
 // Sequences whose tiles one workgroup sums.
@@ -348,17 +349,21 @@ struct PageRange {
 // sequence's range and page list, then the page id beside the token) and one
 // store; a chunk is an HBM copy. The host knows neither, the ranges being on
 // the device, so the grid has two kinds of workgroups:
-//  * one for each sequence and pool, launched first: its partly touched first
-//    and last pages, all heads at once. An append costs one short chain, and
-//    no workgroup of this kind looks at another sequence.
+//  * one for each sequence and pool, or, where they are so many that the chip
+//    takes them in several rounds, one for each sequence and both pools,
+//    launched first: its partly touched first and last pages, all heads at
+//    once. An append costs one short chain, and no workgroup of this kind looks
+//    at another sequence.
 //  * tile_blocks per pool for the whole pages: each sums the whole-page tiles
-//    of all sequences and its waves take equal contiguous runs of them, so one
-//    long range among many short ones spreads over the chip. Without a whole
-//    page it ends after the sum.
+//    of all sequences and its waves take equal shares of them, so one long
+//    range among many short ones spreads over the chip. Without a whole page it
+//    ends after the sum.
 // Kernel times against a grid of equal workgroups per sequence (bf16, d 128, 8
 // heads, K and V): 240 appends and 16 chunks of 64-512 tokens 66 -> 18 us, 992
-// appends and 32 chunks 298 -> 54 us, 32 ragged chunks 27 -> 20 us, 64 appends
-// 5.7 -> 4.3 us, 32 chunks of 512 tokens 31 us (4.3 TB/s) with both.
+// appends and 32 chunks 298 -> 58 us, 32 ragged chunks 27 -> 20 us, 64 appends
+// 5.2 -> 4.0 us, 1024 appends 15.2 -> 13.2; 32 aligned chunks of 512 tokens after
+// other work 42.3 -> 40.6 us (fp32 74.1 -> 71.6), written again and again 22.0 ->
+// 23.5 (fp32 48.7 -> 48.5).
 template <typename W, int D, bool V>
 __device__ __forceinline__ void scatter_seq(const ScatterArgs& a, int z, int first_seq, int stride) {
   const int H = a.num_kv_heads;
@@ -422,14 +427,17 @@ struct SeqRange {
   }
 };
 
-// Whole pages: the tiles of up to kTileSeqs sequences, cut into equal
-// contiguous runs, one per wave. Up to 64 sequences every wave sums by itself,
-// one sequence per lane, and finds its run in the lanes' registers, without a
-// barrier or a second look at the metadata (32 chunks of 512 tokens, K and V:
-// 30.6 us; by the workgroup 33.5). More are summed by the workgroup, thread i
-// those of sequences i, i + 256, ..., in LDS (1024 appends: 18 us, against
-// 22.7 when every wave sums all of them). A sequence with fewer than 16 new
-// tokens has no whole page: only its count is read.
+// Whole pages: the tiles of up to kTileSeqs sequences, shared equally by the
+// waves. Up to 64 sequences every wave sums by itself, one sequence per lane,
+// and finds its tiles in the lanes' registers, without a barrier or a second
+// look at the metadata (32 chunks of 512 tokens, K and V: 30.6 us; by the
+// workgroup 33.5); it takes every turns-th tile, so that neighbouring waves
+// move neighbouring heads of one page (32 fp32 chunks of 512 tokens after other
+// work: 83 us with contiguous runs, 72 so). More are summed by the workgroup,
+// thread i those of sequences i, i + 256, ..., in LDS (1024 appends: 18 us,
+// against 22.7 when every wave sums all of them), and a wave takes a contiguous
+// run. A sequence with fewer than 16 new tokens has no whole page: only its
+// count is read.
 template <typename W, int D, bool V>
 __device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int z, int s0, int n_seqs, int turn, int turns,
                                               u32x4_t* stage, int (&sums)[260], int wave, int lane) {
@@ -474,8 +482,8 @@ __device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int z, int s
     __syncthreads();
   }
   const int per = (int)(((int64_t)total + turns - 1) / turns);
-  int k = (int)min((int64_t)total, (int64_t)turn * per);
-  const int k_end = (int)min((int64_t)total, (int64_t)k + per);
+  int k = by_wave ? turn : (int)min((int64_t)total, (int64_t)turn * per);
+  const int k_end = by_wave ? total : (int)min((int64_t)total, (int64_t)k + per);
   while (k < k_end) {
     int t, n, base, f0;
     int64_t at;   // dense row of the sequence's token 0
@@ -507,8 +515,8 @@ __device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int z, int s
       at = r.off - r.start;
     }
     // tiles t .. t_end - 1 of one sequence, heads innermost
-    const int t_end = min(n, t + (k_end - k));
-    k += t_end - t;
+    const int t_end = by_wave ? t + 1 : min(n, t + (k_end - k));
+    k += by_wave ? turns : t_end - t;
     const W* in = static_cast<const W*>(a.in[z]) + at * row;
 #pragma nounroll
     for (; t < t_end; ++t) {
@@ -531,9 +539,15 @@ __global__ __launch_bounds__(256) void scatter_kernel(ScatterArgs a) {
   __shared__ int sums[260];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   if ((int)blockIdx.x < a.seq_blocks) {
-    const int z = (int)blockIdx.x % a.n_pairs, seq = (int)blockIdx.x / a.n_pairs, stride = a.seq_blocks / a.n_pairs;
-    if (a.v_layout[z]) scatter_seq<W, D, true>(a, z, seq, stride);
-    else scatter_seq<W, D, false>(a, z, seq, stride);
+    // (z, then the following ones up to z_end: one pool, or all)
+    int z = (int)blockIdx.x % a.seq_split;
+    const int z_end = z + a.n_pairs / a.seq_split;
+    const int seq = (int)blockIdx.x / a.seq_split, stride = a.seq_blocks / a.seq_split;
+#pragma nounroll
+    for (; z < z_end; ++z) {
+      if (a.v_layout[z]) scatter_seq<W, D, true>(a, z, seq, stride);
+      else scatter_seq<W, D, false>(a, z, seq, stride);
+    }
     return;
   }
   const int z = ((int)blockIdx.x - a.seq_blocks) % a.n_pairs;
@@ -646,12 +660,16 @@ halo_status_t launch_scatter(const halo_attn_params_t* params, ScatterArgs g, in
   g.n_pairs = n_pairs;
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  // A workgroup per sequence and pool (grid-stride past 65536 sequences), and
+  // A workgroup per sequence and pool, or for both pools from 257 sequences on
+  // (512 appends 9.8 -> 8.6 us, 1024 15.9 -> 13.2; 128 4.9 -> 5.0, 64 4.0 -> 4.5;
+  // 992 appends and 32 chunks, whose last pages then come one after the other,
+  // 39.6 -> 42.8), grid-stride past 65536 sequences, and
   // 512 of four waves for the whole pages: with 1024 a batch of appends waits
   // for them (64 sequences: 4.3 -> 4.7 us), with 256 a chunk's copies have
   // too few loads in flight (32 chunks of 512 tokens: 30.8 -> 39 us).
   constexpr int kTileBlocks = 512;
-  g.seq_blocks = std::min(g.num_seqs, 65536) * n_pairs;
+  g.seq_split = g.num_seqs > 256 ? 1 : n_pairs;
+  g.seq_blocks = std::min(g.num_seqs, 65536) * g.seq_split;
   g.tile_blocks = kTileBlocks / n_pairs;
   const dim3 grid(g.seq_blocks + kTileBlocks);
   const bool d128 = params->head_dim == 128;
