@@ -492,10 +492,33 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       int64_t tokens = 0;
       for (int s = 0; s < S; ++s) tokens += refs[s] ? paged(f.seg_len[s]) : 0;
       const int64_t bytes = tokens * 2 * Hkv * p.head_dim * (p.kv_dtype == HALO_BF16 ? 2 : 4);
-      if (all_items(256, kc_private) <= 4 * kNumCUs) kc_shared = 256;
+      // Where every row is one item at the longer chunks, a cut also brings the
+      // merge launch: it has to save more than 2.5 us of the longest chain (45
+      // fp32 requests of 1-75 keys, d 64: 7.2 us, cut at 64 keys 8.7; 8 of 250
+      // keys, bf16 with an fp32 output: 9.3, cut 7.5).
+      const double step_us = p.kv_dtype == HALO_BF16 ? (p.head_dim == 128 ? 0.6 : 0.45) : (p.head_dim == 128 ? 2.4 : 1.25);
+      int64_t own = 0, common = 0;   // keys of the longest private path part and shared segment
+      bool merged = false;
+      for (int r = 0; r < R && !merged; ++r) {
+        int64_t priv = 0, n = 0;
+        for (int32_t i = path_begin(r); i < path_end(r); ++i) {
+          const int64_t len = paged(f.seg_len[f.req_seg_ids[i]]);
+          if (refs[f.req_seg_ids[i]] == 1) priv += len;
+          else common = std::max(common, len), n += ceil_div(len, 512);
+        }
+        own = std::max(own, priv);
+        merged = n + ceil_div(priv, kc_private_default) > 1;
+      }
+      auto steps = [&](int64_t ks, int64_t kp) {
+        return ceil_div(std::max(std::min(common, ks), std::min(own, kp)), kKeysPerStep);
+      };
+      auto pays = [&](int64_t ks, int64_t kp) {
+        return merged || (steps(512, kc_private_default) - steps(ks, kp)) * step_us > 2.5;
+      };
+      if (all_items(256, kc_private) <= 4 * kNumCUs && pays(256, kc_private)) kc_shared = 256;
       if (kc_private == 256 && bytes <= kLatencyBytes)
         for (int kc : {64, 96, 128, 192})
-          if (all_items(kc, kc) <= kMaxShortItems) {
+          if (all_items(kc, kc) <= kMaxShortItems && pays(kc, kc)) {
             kc_shared = kc_private = kc;
             break;
           }

@@ -56,6 +56,17 @@ def test_only_those_rows_stay_whole():
     assert max(int(sp[2] - sp[1]) for sp in m["spans"] if sp[0] == 0) == 400
 
 
+@pytest.mark.parametrize("dtype,out_dtype", [(torch.float32, torch.float32), (torch.bfloat16, torch.float32)])
+def test_a_cut_that_saves_less_than_the_merge_costs(dtype, out_dtype):
+    """Rows of one short item each are not cut only to be merged; with a row
+    that is merged anyway the chunks are short."""
+    paths = [[i] for i in range(12)]
+    assert _plan([75] * 12, paths, dtype, out_dtype).workspace_bytes == 0
+    assert _plan([250] * 12, paths, dtype, out_dtype).workspace_bytes > 0
+    m = _plan([75] * 11 + [300], paths, dtype, out_dtype).inspect()
+    assert max(int(sp[2] - sp[1]) for sp in m["spans"]) <= 64
+
+
 def _covers(plan, csr):
     """Each request's items cover the keys of its path, each once."""
     m = plan.inspect()
