@@ -480,6 +480,7 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
     // items) 13.8, at 128 keys 15.1.
     int kc_shared = 512;
     int kc_private = kc_private_default;
+    std::vector<char> one_item_req(R, 0), one_item_seg(S, 0);
     if (!wide) {
       auto all_items = [&](int64_t ks, int64_t kp) {
         int64_t n = private_items(kp) * ceil_div(G, kRowsPerItem);
@@ -492,28 +493,46 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       int64_t tokens = 0;
       for (int s = 0; s < S; ++s) tokens += refs[s] ? paged(f.seg_len[s]) : 0;
       const int64_t bytes = tokens * 2 * Hkv * p.head_dim * (p.kv_dtype == HALO_BF16 ? 2 : 4);
-      // Where every row is one item at the longer chunks, a cut also brings the
-      // merge launch: it has to save more than 2.5 us of the longest chain (45
-      // fp32 requests of 1-75 keys, d 64: 7.2 us, cut at 64 keys 8.7; 8 of 250
-      // keys, bf16 with an fp32 output: 9.3, cut 7.5).
+      // With a bf16 output, rows that one item holds at the longer chunks stay
+      // there: cut, they would be rounded to bf16 twice, as partial results and
+      // as merged ones (200-250 keys: relative error 1.84e-3 -> 2.41e-3; rows of
+      // several partials are anyway, and splitting them further leaves their
+      // error at 2.4e-3).
+      // A cut has to shorten the longest chain: by more than 1 us, and where no
+      // row is merged without it, by 2.5 us for the merge launch (45 fp32
+      // requests of 1-75 keys, d 64: 7.05 us, cut at 64 keys 8.5; 154 bf16
+      // requests of 3-1285 keys, one kv head, whose rows of up to 256 keys stay
+      // whole: 10.2, the others cut at 128 keys 11.3; 8 of 250 keys, bf16 with
+      // an fp32 output: 9.3, cut 7.5).
       const double step_us = p.kv_dtype == HALO_BF16 ? (p.head_dim == 128 ? 0.6 : 0.45) : (p.head_dim == 128 ? 2.4 : 1.25);
-      int64_t own = 0, common = 0;   // keys of the longest private path part and shared segment
+      int64_t own = 0, common = 0, whole_keys = 0;   // most keys of a request's own, of a shared segment, of a row that stays whole
       bool merged = false;
-      for (int r = 0; r < R && !merged; ++r) {
-        int64_t priv = 0, n = 0;
+      for (int r = 0; r < R; ++r) {
+        int64_t priv = 0, shared_keys = 0, chunks = 0;
         for (int32_t i = path_begin(r); i < path_end(r); ++i) {
-          const int64_t len = paged(f.seg_len[f.req_seg_ids[i]]);
-          if (refs[f.req_seg_ids[i]] == 1) priv += len;
-          else common = std::max(common, len), n += ceil_div(len, 512);
+          const int64_t n = paged(f.seg_len[f.req_seg_ids[i]]);
+          if (refs[f.req_seg_ids[i]] == 1) {
+            priv += n;
+          } else {
+            shared_keys = std::max(shared_keys, n);
+            chunks += ceil_div(n, 512);
+          }
         }
         own = std::max(own, priv);
-        merged = n + ceil_div(priv, kc_private_default) > 1;
+        common = std::max(common, shared_keys);
+        chunks += ceil_div(priv, kc_private_default);
+        merged |= chunks > 1;
+        if (chunks > 1 || p.out_dtype != HALO_BF16) continue;
+        one_item_req[r] = 1;
+        for (int32_t i = path_begin(r); i < path_end(r); ++i) one_item_seg[f.req_seg_ids[i]] = 1;
+        whole_keys = std::max(whole_keys, priv + shared_keys);
       }
       auto steps = [&](int64_t ks, int64_t kp) {
         return ceil_div(std::max(std::min(common, ks), std::min(own, kp)), kKeysPerStep);
       };
       auto pays = [&](int64_t ks, int64_t kp) {
-        return merged || (steps(512, kc_private_default) - steps(ks, kp)) * step_us > 2.5;
+        const int64_t after = std::max(steps(ks, kp), (int64_t)ceil_div(whole_keys, kKeysPerStep));
+        return (steps(512, kc_private_default) - after) * step_us > (merged ? 1.0 : 2.5);
       };
       if (all_items(256, kc_private) <= 4 * kNumCUs && pays(256, kc_private)) kc_shared = 256;
       if (kc_private == 256 && bytes <= kLatencyBytes)
@@ -523,25 +542,6 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
             break;
           }
     }
-    // With a bf16 output, rows that one item holds at the longer chunks stay
-    // there: cut, they would be rounded to bf16 twice, as partial results and as
-    // merged ones (200-250 keys: relative error 1.84e-3 -> 2.41e-3; rows of
-    // several partials are anyway, and splitting them further leaves their error
-    // at 2.4e-3). It costs 16 requests of 250 keys 0.9 us of 8.2, 4 on 500 shared
-    // keys alone 4.9 of 7.
-    std::vector<char> one_item_req(R, 0), one_item_seg(S, 0);
-    if (p.out_dtype == HALO_BF16 && (kc_shared < 512 || kc_private < kc_private_default))
-      for (int r = 0; r < R; ++r) {
-        int64_t shared_chunks = 0, priv = 0;
-        for (int32_t i = path_begin(r); i < path_end(r); ++i) {
-          const int64_t n = paged(f.seg_len[f.req_seg_ids[i]]);
-          if (refs[f.req_seg_ids[i]] == 1) priv += n;
-          else shared_chunks += ceil_div(n, 512);
-        }
-        one_item_req[r] = shared_chunks == 0 ? priv <= kc_private_default : shared_chunks == 1 && priv == 0;
-        if (one_item_req[r])
-          for (int32_t i = path_begin(r); i < path_end(r); ++i) one_item_seg[f.req_seg_ids[i]] = 1;
-      }
     if (opt.kc_shared > 0) kc_shared = opt.kc_shared;
     if (opt.kc_private > 0) kc_private = opt.kc_private;
     short_private = opt.kc_private == 0 && kc_private < kc_private_default;

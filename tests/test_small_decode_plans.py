@@ -67,6 +67,15 @@ def test_a_cut_that_saves_less_than_the_merge_costs(dtype, out_dtype):
     assert max(int(sp[2] - sp[1]) for sp in m["spans"]) <= 64
 
 
+def test_rows_that_stay_whole_bound_the_cut():
+    """Where a whole row's chain is as long as any other's, the others are not
+    cut either (bf16 output); a shorter one does not stop the cut."""
+    longest = lambda lens: max(int(sp[2] - sp[1]) for sp in _plan(
+        lens, [[i] for i in range(len(lens))], torch.bfloat16, torch.bfloat16).inspect()["spans"])
+    assert longest([250, 900, 900]) == 256
+    assert longest([100, 900, 900]) == 100
+
+
 def _covers(plan, csr):
     """Each request's items cover the keys of its path, each once."""
     m = plan.inspect()
