@@ -504,8 +504,10 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
       // requests of 3-1285 keys, one kv head, whose rows of up to 256 keys stay
       // whole: 10.2, the others cut at 128 keys 11.3; 8 of 250 keys, bf16 with
       // an fp32 output: 9.3, cut 7.5).
-      const double step_us = p.kv_dtype == HALO_BF16 ? (p.head_dim == 128 ? 0.6 : 0.45) : (p.head_dim == 128 ? 2.4 : 1.25);
-      int64_t own = 0, common = 0, whole_keys = 0;   // most keys of a request's own, of a shared segment, of a row that stays whole
+      const bool bf16 = p.kv_dtype == HALO_BF16, d128 = p.head_dim == 128;
+      const double step_us = bf16 ? (d128 ? 0.6 : 0.45) : (d128 ? 2.4 : 1.25);
+      // the most keys of a request's own, of a shared segment, of a row that stays whole
+      int64_t own = 0, common = 0, whole_keys = 0;
       bool merged = false;
       for (int r = 0; r < R; ++r) {
         int64_t priv = 0, shared_keys = 0, chunks = 0;
