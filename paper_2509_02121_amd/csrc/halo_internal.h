@@ -177,10 +177,12 @@ struct DefaultInitAlloc : std::allocator<T> {
 // its last key and those past len_lo, each with the key its end never passes
 // (tail_end), and the image byte offsets of the item whose first span it is and
 // of that item's lane record (-1 if none).
-// patches: every image word an update has written since the plan was made,
-// as it is now (rebuilt by each update; more than MetaLayout::max_patches:
-// incomplete, the sections are uploaded instead). touched: the
-// segments that ever changed; min_pages: the fewest pages each has had.
+// patches: every image word an update has written since the plan was made, as
+// it is now (overflow: more than MetaLayout::max_patches, incomplete, and the
+// sections are uploaded instead). touched: the segments that ever changed;
+// min_pages: the fewest pages each has had; patch_at: where its length patches
+// begin (-1: none), in the order of its spans; patch_np: how many of its pages
+// are patched or as planned.
 struct Patch {
   uint32_t word;   // offset in the image, in 32-bit words
   int32_t value;
@@ -191,6 +193,8 @@ struct AppendIndex {
   std::vector<int32_t> tail_indptr, tail_span, tail_end;
   std::vector<int64_t> tail_item, tail_rec;
   std::vector<Patch> patches;
+  bool overflow = false;
+  std::vector<int32_t> patch_at, patch_np;
   std::vector<int32_t> touched, min_pages;   // min_pages: -1 until touched
 };
 

@@ -1728,7 +1728,7 @@ extern "C" halo_status_t halo_plan_upload_update(const halo_plan_t* plan, void* 
   uint8_t* meta = static_cast<uint8_t*>(device_meta);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
-  if (patches.size() <= plan->layout.max_patches && capture == hipStreamCaptureStatusNone) {
+  if (!plan->append.overflow && patches.size() <= plan->layout.max_patches && capture == hipStreamCaptureStatusNone) {
     if (patches.empty()) return HALO_OK;
     halo_status_t rc = HALO_OK;
     if (upload_patches(patches, meta, st, &rc)) return rc;

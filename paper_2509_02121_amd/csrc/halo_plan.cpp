@@ -1347,8 +1347,10 @@ extern "C" halo_status_t halo_plan_create_with_options(const halo_attn_params_t*
         capped[s] = 1;
       }
     }
-    ax.patches.reserve(L.max_patches + 1);   // one more says that they are too many
+    ax.patches.reserve(L.max_patches + 1);
     ax.touched.reserve(S);
+    ax.patch_at.assign(S, -1);
+    ax.patch_np.assign(S, 0);
     ax.min_pages.assign(S, -1);
   }
 
@@ -1472,6 +1474,38 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
   const MetaLayout& L = plan->layout;
   AppendIndex& mx = plan->append;
   int32_t* slots = reinterpret_cast<int32_t*>(m + L.page_ids);
+  // The patches: every word an update has written since the plan was made. A
+  // segment's length patches are made once and get new values, its page patches
+  // are added as pages open; where pages were dropped (others may take their
+  // places) all are made again. More than max_patches: none any more.
+  bool stale = false;
+  auto push = [&](size_t byte, int32_t value) { mx.patches.push_back(Patch{(uint32_t)(byte / 4), value}); };
+  auto full = [&]() { return mx.overflow |= mx.patches.size() > L.max_patches; };
+  auto push_lengths = [&](int32_t s) {
+    if (full()) return;
+    mx.patch_at[s] = (int32_t)mx.patches.size();
+    push(L.seg_len + 4 * (size_t)s, mx.seg_len[s]);
+    for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
+      const size_t at = L.spans + sizeof(Span) * (size_t)mx.tail_span[k];
+      const int32_t end = reinterpret_cast<const Span*>(m + at)->key_end;
+      push(at + offsetof(Span, key_end), end);
+      if (mx.tail_item[k] >= 0) push((size_t)mx.tail_item[k] + offsetof(Item, s0_key_end), end);
+    }
+  };
+  auto push_pages = [&](int32_t s, int64_t from, int64_t to) {   // pages from .. to - 1 of segment s
+    if (full()) return;
+    const int32_t* page = slots + mx.page_slot_off[s];
+    for (int64_t j = from; j < to; ++j) push(L.page_ids + 4 * (size_t)(mx.page_slot_off[s] + j), page[j]);
+    for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
+      if (mx.tail_rec[k] < 0) continue;
+      // the record's page j is page first + j of the segment
+      const Span* sp = reinterpret_cast<const Span*>(m + L.spans) + mx.tail_span[k];
+      const int64_t first = sp->key_begin / ps;
+      const int64_t n = std::min<int64_t>(32, ceil_div(sp->key_end - sp->key_begin, ps));
+      for (int64_t j = std::max(first, from); j < std::min(first + n, to); ++j)
+        push((size_t)mx.tail_rec[k] + offsetof(ItemRec, page) + 4 * (size_t)(j - first), page[j]);
+    }
+  };
   for (int s = 0; s < S; ++s) {
     const int32_t len = f.seg_len[s], old = mx.seg_len[s];
     if (len == old) continue;
@@ -1484,10 +1518,17 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
     if (np > np_old)
       memcpy(slots + mx.page_slot_off[s] + np_old, f.seg_page_ids + f.seg_page_indptr[s] + np_old,
              sizeof(int32_t) * (np - np_old));
+    const bool patched = mx.patch_at[s] >= 0 && !mx.overflow;
+    Patch* out = patched ? mx.patches.data() + mx.patch_at[s] : nullptr;
+    if (out) (out++)->value = len;
     for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
       Span* sp = reinterpret_cast<Span*>(m + L.spans) + mx.tail_span[k];
       sp->key_end = std::max(sp->key_begin, std::min(len, mx.tail_end[k]));
-      if (mx.tail_item[k] >= 0) reinterpret_cast<Item*>(m + mx.tail_item[k])->s0_key_end = sp->key_end;
+      if (out) (out++)->value = sp->key_end;
+      if (mx.tail_item[k] >= 0) {
+        reinterpret_cast<Item*>(m + mx.tail_item[k])->s0_key_end = sp->key_end;
+        if (out) (out++)->value = sp->key_end;
+      }
       if (mx.tail_rec[k] >= 0 && np != np_old) {
         // the record holds the span's first 32 page ids
         ItemRec* rc = reinterpret_cast<ItemRec*>(m + mx.tail_rec[k]);
@@ -1499,28 +1540,22 @@ extern "C" halo_status_t halo_plan_update_lengths(halo_plan_t* plan, const halo_
     plan->distinct_kv_tokens += len - old;
     plan->visible_pairs += (int64_t)(len - old) * mx.refs[s] * plan->params.num_q_heads;
     mx.seg_len[s] = len;
+    if (!patched) {
+      push_lengths(s);
+      mx.patch_np[s] = (int32_t)np_old;
+    }
+    if (np > mx.patch_np[s]) {
+      push_pages(s, mx.patch_np[s], np);
+      mx.patch_np[s] = (int32_t)np;
+    }
+    stale |= np < mx.patch_np[s];
   }
-  // The patches: every word an update has written since the plan was made.
-  auto patch = [&](size_t byte) {
-    if (mx.patches.size() <= L.max_patches)
-      mx.patches.push_back(Patch{(uint32_t)(byte / 4), *reinterpret_cast<const int32_t*>(m + byte)});
-  };
-  mx.patches.clear();
-  for (int32_t s : mx.touched) {
-    if (mx.patches.size() > L.max_patches) break;
-    patch(L.seg_len + 4 * (size_t)s);
-    const int64_t np = ceil_div(mx.seg_len[s], ps), from = mx.min_pages[s];
-    for (int64_t j = from; j < np; ++j) patch(L.page_ids + 4 * (size_t)(mx.page_slot_off[s] + j));
-    for (int32_t k = mx.tail_indptr[s]; k < mx.tail_indptr[s + 1]; ++k) {
-      const size_t at = L.spans + sizeof(Span) * (size_t)mx.tail_span[k];
-      patch(at + offsetof(Span, key_end));
-      if (mx.tail_item[k] >= 0) patch((size_t)mx.tail_item[k] + offsetof(Item, s0_key_end));
-      if (mx.tail_rec[k] >= 0) {
-        const Span* sp = reinterpret_cast<const Span*>(m + at);
-        const int64_t first = sp->key_begin / ps, n = ceil_div(sp->key_end - sp->key_begin, ps);
-        for (int64_t j = std::max<int64_t>(0, from - first); j < std::min<int64_t>(32, n); ++j)
-          patch((size_t)mx.tail_rec[k] + offsetof(ItemRec, page) + 4 * (size_t)j);
-      }
+  if (stale && !mx.overflow) {
+    mx.patches.clear();
+    for (int32_t s : mx.touched) {
+      push_lengths(s);
+      mx.patch_np[s] = (int32_t)ceil_div(mx.seg_len[s], ps);
+      push_pages(s, mx.min_pages[s], mx.patch_np[s]);
     }
   }
   if (pages_moved) {

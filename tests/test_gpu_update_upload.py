@@ -155,9 +155,20 @@ def test_uploads_of_many_plans_at_once(gpu_lib):
     for p, m in zip(plans, metas):
         p.upload(m)
     torch.cuda.synchronize()
-    for cut in (50, 31, 33, 0, 12):
+    # pages that open again after a removal are others than before
+    owned = [[list(x) for x in np.split(short["seg_page_ids"], short["seg_page_indptr"][1:-1])] for _ in plans]
+    fresh = w.num_pool_pages - 1
+    for cut in (50, 31, 55, 33, 0, 12, 60, 0):
         for i, (p, m, s) in enumerate(zip(plans, metas, streams)):
-            assert p.update_lengths(_shortened(full, w, np.array([0, cut, (cut + i) % 60, cut])))
+            csr = _shortened(full, w, np.array([0, cut, (cut + 7 * i) % 61, cut]))
+            for seg, n in enumerate(csr["seg_len"]):
+                pages = owned[i][seg][:(int(n) + 15) // 16]
+                while len(pages) < (int(n) + 15) // 16:
+                    pages.append(fresh)
+                    fresh = fresh - 1 if fresh else w.num_pool_pages - 1
+                owned[i][seg] = pages
+            csr["seg_page_ids"] = np.concatenate(owned[i]).astype(np.int32)
+            assert p.update_lengths(csr)
             p.upload_update(m, s)
     torch.cuda.synchronize()
     for p, m in zip(plans, metas):
