@@ -892,15 +892,18 @@ class PrefixAttention:
         replay on any stream, beside any other call of this object."""
         import torch
         fn = _LIB.halo_prefix_attn_prefill if self.plan.is_prefill else _LIB.halo_prefix_attn_decode
-        ws = self._workspace_on(stream)
-        _check_run(self.plan, self.meta, q, k_pool, v_pool, o, lse, ws)
+        capturing = torch.cuda.is_current_stream_capturing
+        n = self.plan.workspace_bytes
+        # (bound during a capture: the graph's memory is not for eager calls)
+        ws = None if capturing() else self._workspace_on(stream)
+        _check_run(self.plan, self.meta, q, k_pool, v_pool, o, lse, ws, library_workspace=ws is None)
         s = self._before_run(stream)
         self._bound[self._cur].add(s)
         tensors = (self.plan._handle, self.meta.data_ptr(), q.data_ptr(), k_pool.data_ptr(),
                    v_pool.data_ptr(), o.data_ptr(), lse.data_ptr() if lse is not None else None)
         handle = _stream_handle(s)
         enqueue = self._enqueue
-        if ws is None:
+        if not n:
             args = (*tensors, None, 0, handle)
 
             def call():
@@ -909,16 +912,23 @@ class PrefixAttention:
                     _check(st)
             return call
 
-        args = (*tensors, ws.data_ptr(), ws.numel(), handle)
-        capturing = torch.cuda.is_current_stream_capturing
+        def new_workspace():
+            return torch.empty(n, dtype=torch.uint8, device=self.device)
 
-        def call(_workspace=ws):   # (kept alive by the callable)
+        args = (*tensors, ws.data_ptr(), n, handle) if ws is not None else None
+
+        def call():
+            nonlocal ws, args   # (the workspace is kept alive by the callable)
             if capturing():
                 with torch.cuda.stream(s):
                     if capturing():
-                        own = torch.empty_like(_workspace)
-                        _check(fn(*tensors, own.data_ptr(), own.numel(), handle))
+                        own = new_workspace()
+                        _check(fn(*tensors, own.data_ptr(), n, handle))
                         return
+            if args is None:
+                with torch.cuda.stream(s):
+                    ws = new_workspace()
+                args = (*tensors, ws.data_ptr(), n, handle)
             with enqueue:
                 st = fn(*args)
             if st != HALO_OK:

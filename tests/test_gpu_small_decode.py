@@ -144,3 +144,27 @@ def test_workspaces_of_many_streams_are_bounded(gpu_lib):
     torch.cuda.synchronize()
     assert len(pa._ws) <= pa.MAX_WORKSPACES
     assert all(torch.equal(o, want) for o in outs)
+
+
+def test_a_call_bound_during_a_capture_runs_eagerly_too(gpu_lib):
+    """Bound while a stream is captured: the graph replays, and eager calls of
+    the same callable leave the graph's memory alone."""
+    print("case: bound during a capture", flush=True)
+    w = to_device(build_workload("bound", 86, 8, 2, 128, torch.bfloat16, [300, 350], [[0], [1]], value_scale=0.5))
+    pa = halo.PrefixAttention(params_of(w), w.forest_csr(), "cuda")
+    stream, side = torch.cuda.Stream(), torch.cuda.Stream()
+    want, want_lse = pa.run(w.q, w.k_pool, w.v_pool, stream=stream)
+    o, lse = pa.alloc_outputs(w.q)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        call = pa.bind(w.q, w.k_pool, w.v_pool, o, lse, stream)
+        call()
+    for _ in range(3):
+        for again in (graph.replay, call):
+            o.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                again()
+            torch.cuda.synchronize()
+            assert torch.equal(o, want) and torch.equal(lse, want_lse)

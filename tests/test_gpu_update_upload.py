@@ -117,29 +117,38 @@ def _small(seed, n_req=3):
                                     [[0, 1 + r] for r in range(n_req)], value_scale=0.5))
 
 
-def test_a_decode_on_another_stream_does_not_wait_for_the_current_one(gpu_lib):
-    """The current stream holds long work; a decode loop on a second stream is
-    not behind it, nor is the host that updates the plan."""
-    print("case: update beside long work on the current stream", flush=True)
+def test_uploads_go_in_order_only_on_the_stream_of_all_calls(gpu_lib):
+    """An upload is put on the current stream only if every call of the object
+    was there and the GPU is not behind: a decode on a second stream never
+    waits for what the current one holds. (By the stream chosen; streams that
+    share a hardware queue wait for each other whatever is chosen.)"""
+    print("case: the stream of an upload", flush=True)
     w = _small(94)
     full = w.forest_csr()
-    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    cut = [_shortened(full, w, np.array([0] + [c] * 3)) for c in (9, 8, 7, 6)]
     second = torch.cuda.Stream()
-    cut = [np.array([0] + [c] * 3) for c in (9, 8, 7)]
-    for c in cut:   # both buffers in use
-        pa.update(_shortened(full, w, c))
-        want, _ = pa.run(w.q, w.k_pool, w.v_pool, stream=second)
-    torch.cuda.synchronize()
-    torch.cuda._sleep(400_000_000)   # some 0.2 s
-    long_work = torch.cuda.Event()
-    long_work.record()
-    for c in cut:
-        pa.update(_shortened(full, w, c))
-        got, _ = pa.run(w.q, w.k_pool, w.v_pool, stream=second)
-    second.synchronize()
-    assert not long_work.query(), "the decode waited for the current stream"
-    torch.cuda.synchronize()
-    assert torch.equal(got, want)
+
+    def uploads(pa, streams):
+        """The stream of each update's upload, runs on the streams given."""
+        used = []
+        for csr, s in zip(cut, streams):
+            torch.cuda.synchronize()   # the GPU is not behind
+            assert pa.update(csr)
+            used.append(pa._upload_streams[pa._cur])
+            pa.run(w.q, w.k_pool, w.v_pool, stream=s)
+        torch.cuda.synchronize()
+        return used
+
+    now = torch.cuda.current_stream()
+    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    assert uploads(pa, [second] * 4) == [pa._copy_stream] * 4
+    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    # (no call yet: nothing says where they will be)
+    assert uploads(pa, [None, None, second, None]) == [pa._copy_stream, now, now, pa._copy_stream]
+    assert uploads(pa, [None] * 4) == [pa._copy_stream] * 4
+    pa = halo.PrefixAttention(params_of(w), full, "cuda")
+    pa.run(w.q, w.k_pool, w.v_pool)
+    assert pa.update(cut[0], second) and pa._upload_streams[pa._cur] == second   # as given
 
 
 def test_uploads_of_many_plans_at_once(gpu_lib):
